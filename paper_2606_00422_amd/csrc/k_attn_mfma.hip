@@ -1,4 +1,4 @@
-// Attention on the matrix cores for bf16 models with head_dim 64: the
+// Attention on the matrix cores for bf16 models (head_dim 64 or 32): the
 // ranking pass (candidate cross-attention) and the encode pass (causal
 // history self-attention) share one kernel.
 //
@@ -53,8 +53,10 @@ typedef __attribute__((ext_vector_type(2))) __bf16 b2;
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 b4v;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-constexpr int kD = 64;            // head_dim
-constexpr int kKS = 64;           // keys per LDS stage
+// Keys per LDS stage: 8 KB of keys and 8 KB of values for either head_dim
+// (64 keys of 128 bytes or 128 keys of 64 bytes), so that the stage barriers
+// stand as far apart.
+constexpr int stage_keys(int D) { return 4096 / D; }
 // 16-query groups per wave: ranking 2 (128 VGPRs, four waves per SIMD: the
 // latency of one wave's exponentials and LDS reads hides behind three
 // others), or 1 for calls too small to fill the device with 128-candidate
@@ -67,14 +69,19 @@ static_assert(8 * 16 * kRankQG == kLongRankAttnTile, "long-history tile: eight w
 static_assert(4 * 16 * kSmallRankQG == kSmallRankAttnTile, "small-call tile must match the kernel");
 static_assert(4 * 16 * kEncodeQG == kAttnTile, "encode work-list tile must match the kernel");
 
-// LDS layout of a stage: 64 rows (keys) x 128 bytes (64 dims), the eight
-// 16-byte chunks of a row XOR-swizzled.  K fragment reads take 16
-// consecutive rows at one chunk: key (row / 2) % 8 puts them on distinct bank
-// groups.  V transposing reads take 8 consecutive rows x 32 bytes per
-// 32-lane pass: key 2 ((row / 2) % 4) keeps the two chunks of a 32-byte pair
-// together and puts equal-parity rows on distinct pairs.
-__device__ __forceinline__ int key_k(int row) { return (row >> 1) & 7; }
-__device__ __forceinline__ int key_v(int row) { return ((row >> 1) & 3) << 1; }
+// LDS layout of a stage: rows (keys) of 2D bytes, their 16-byte chunks
+// XOR-swizzled.  K fragment reads take 16 consecutive rows at one chunk; a
+// 256-byte bank period holds two rows at D = 64 (key (row / 2) % 8) and four
+// at D = 32 (key (row / 4) % 4), which puts the 16 on distinct bank groups.  V
+// transposing reads take 8 consecutive rows x 32 bytes per 32-lane pass: keys
+// 2 ((row / 2) % 4) and 2 ((row / 4) % 2) keep the two chunks of a 32-byte
+// pair together and put rows of one bank offset on distinct pairs.
+template <int D> __device__ __forceinline__ int key_k(int row) {
+    return D == 64 ? (row >> 1) & 7 : (row >> 2) & 3;
+}
+template <int D> __device__ __forceinline__ int key_v(int row) {
+    return D == 64 ? ((row >> 1) & 3) << 1 : ((row >> 2) & 1) << 1;
+}
 
 __device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(a, fmaxf(b, c)); }
 
@@ -112,13 +119,26 @@ __device__ __forceinline__ float quad_sum(float v) {
 // projection variant; else fp16.  kW: waves per workgroup, four, or eight
 // for ranking over long histories (256-candidate items, two workgroups per
 // CU, so still four waves per SIMD).
-template <bool CAUSAL, int kQG, bool MXO = false, int kW = 4>
+// kD: head_dim.  At 32 the probabilities weight V as two bf16 terms, p = hi +
+// lo (hi the rounded p, lo the rounded rest: 16 significand bits), two MFMAs
+// and two row-sum dot products instead of one: such models have always had
+// fp32 probabilities, and one bf16 term would round them 2^8 times coarser
+// than this.  The extra MFMAs are cheap there (two 16-row blocks of V
+// instead of four); the kernel is bound by the exponentials and conversions.
+// Ranking 16 users x (32-512 rows, 200-1500 candidates), 8 heads of 32:
+// 0.321 ms per layer on the one-wave-per-row kernel, 0.0175 here; scores as
+// far from a 64-bit result as before (1.8e-3).
+template <bool CAUSAL, int kQG, bool MXO = false, int kW = 4, int kD = 64>
 __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4)) void k_attn_mfma(
     const bf16* __restrict__ qsrc, int64_t qstride, void* __restrict__ out,
     uint8_t* __restrict__ out_scales, int64_t row0, int H, const int4* __restrict__ work,
     const bf16* __restrict__ cache_k, const bf16* __restrict__ cache_v, int64_t cap, int force_exact) {
     // Stages as separate arrays: the compiler can then tell that reads of one
     // stage do not alias the loads filling the other.
+    constexpr int kKS = stage_keys(kD), kES = kD / 32, kEB = kD / 16;
+    constexpr int kCR = kD / 8;         // 16-byte chunks per row
+    constexpr bool kSplitP = kD == 32;
+    static_assert(kD == 64 || (kD == 32 && !MXO), "head_dim 64 or 32; MXFP8 output at 64 only");
     __shared__ __attribute__((aligned(16))) bf16 sK0[kKS * kD];
     __shared__ __attribute__((aligned(16))) bf16 sK1[kKS * kD];
     __shared__ __attribute__((aligned(16))) bf16 sV0[kKS * kD];
@@ -155,28 +175,28 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
     const __amdgpu_buffer_rsrc_t rsV = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(cache_v + ((int64_t)h * cap + hb) * kD), (short)0, n * kD * 2, 0x00020000);
     // Each of the kW waves fills kRPW rows of a stage (wave w: rows kRPW w ..)
-    // with 8-row loads, two per matrix (four waves) or one (eight); slot s of
-    // row r holds logical chunk s ^ key(r).  (Fixed-size arrays: with a
-    // template-dependent size the host pass of this compiler drops the
-    // kernel's launch stub.)
-    constexpr int kRPW = kKS / kW, kLPM = kRPW / 8;
+    // with 64-chunk loads (kRPL rows), two per matrix (four waves) or one
+    // (eight); slot s of row r holds logical chunk s ^ key(r).  (Fixed-size
+    // arrays: with a template-dependent size the host pass of this compiler
+    // drops the kernel's launch stub.)
+    constexpr int kRPW = kKS / kW, kRPL = 64 / kCR, kLPM = kRPW / kRPL;
     static_assert(kLPM == 1 || kLPM == 2, "four or eight waves");
     int offK[2], offV[2];
 #pragma unroll
     for (int i = 0; i < kLPM; ++i) {
-        const int row = kRPW * wave + 8 * i + (lane >> 3), slot = lane & 7;
-        offK[i] = row * kD * 2 + ((slot ^ key_k(row)) << 4);
-        offV[i] = row * kD * 2 + ((slot ^ key_v(row)) << 4);
+        const int row = kRPW * wave + kRPL * i + lane / kCR, slot = lane % kCR;
+        offK[i] = row * kD * 2 + ((slot ^ key_k<kD>(row)) << 4);
+        offV[i] = row * kD * 2 + ((slot ^ key_v<kD>(row)) << 4);
     }
     auto issue_loads = [&](bf16* dK, bf16* dV, int st) __attribute__((always_inline)) {
         const int base = st * kKS * kD * 2;
 #pragma unroll
         for (int i = 0; i < kLPM; ++i) {
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                rsK, (__attribute__((address_space(3))) void*)(dK + (kRPW * wave + 8 * i) * kD),
+                rsK, (__attribute__((address_space(3))) void*)(dK + (kRPW * wave + kRPL * i) * kD),
                 16, offK[i] + base, 0, 0, 0);
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                rsV, (__attribute__((address_space(3))) void*)(dV + (kRPW * wave + 8 * i) * kD),
+                rsV, (__attribute__((address_space(3))) void*)(dV + (kRPW * wave + kRPL * i) * kD),
                 16, offV[i] + base, 0, 0, 0);
         }
     };
@@ -187,10 +207,10 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
     if (first_issued) issue_loads(sK0, sV0, 0);
 
     // ---- queries of this wave (B operand of S^T), own key/value, initial state
-    b8 qf[kQG][2];
+    b8 qf[kQG][kES];
     f32x4 negm[kQG];                      // -m of the lane's query, in all four registers
     float l[kQG];                         // lane-partial sums of probabilities
-    f32x4 o[kQG][4];                      // O^T: e = 16eb + 4g + r of query l16
+    f32x4 o[kQG][kEB];                    // O^T: e = 16eb + 4g + r of query l16
     // Loads the queries and starts the softmax against reference
     // max(own logit, mref[qg]) (mref = -inf: the own logit).  Ranking starts
     // from the candidate's own key and value (p_self = 1 against its own
@@ -206,7 +226,7 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
             const bf16* krow = CAUSAL ? cache_k + ((int64_t)h * cap + c0 + qi) * kD : qrow + d;
             float s = 0.f;
 #pragma unroll
-            for (int es = 0; es < 2; ++es) {
+            for (int es = 0; es < kES; ++es) {
                 qf[qg][es] = *reinterpret_cast<const b8*>(qrow + es * 32 + 8 * g);
                 const b8 kf = *reinterpret_cast<const b8*>(krow + es * 32 + 8 * g);
 #pragma unroll
@@ -219,12 +239,12 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
             if constexpr (CAUSAL) {
                 l[qg] = 0.f;
 #pragma unroll
-                for (int eb = 0; eb < 4; ++eb) o[qg][eb] = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int eb = 0; eb < kEB; ++eb) o[qg][eb] = f32x4{0.f, 0.f, 0.f, 0.f};
             } else {
                 l[qg] = g == 0 ? ps : 0.f;
                 const bf16* vrow = qrow + 2 * d;
 #pragma unroll
-                for (int eb = 0; eb < 4; ++eb) {
+                for (int eb = 0; eb < kEB; ++eb) {
                     const bf16* vp = vrow + eb * 16 + 4 * g;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) o[qg][eb][r] = ps * (float)vp[r];
@@ -249,15 +269,17 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
-            b8 kf[2];
+            b8 kf[kES];
             const int row = kb + t * 16 + l16;
 #pragma unroll
-            for (int es = 0; es < 2; ++es)
-                kf[es] = *reinterpret_cast<const b8*>(&cK[row * kD + (((es * 4 + g) ^ key_k(row)) << 3)]);
+            for (int es = 0; es < kES; ++es)
+                kf[es] = *reinterpret_cast<const b8*>(&cK[row * kD + (((es * 4 + g) ^ key_k<kD>(row)) << 3)]);
 #pragma unroll
             for (int qg = 0; qg < kQG; ++qg) {
-                f32x4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[0], qf[qg][0], negm[qg], 0, 0, 0);
-                s[qg][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[1], qf[qg][1], acc, 0, 0, 0);
+                s[qg][t] = negm[qg];
+#pragma unroll
+                for (int es = 0; es < kES; ++es)
+                    s[qg][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[es], qf[qg][es], s[qg][t], 0, 0, 0);
             }
         }
         __builtin_amdgcn_s_setprio(0);
@@ -274,18 +296,26 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
                         if (CAUSAL ? key > qpos[qg] : key >= n) s[qg][t][r] = -INFINITY;
                 }
         }
-        b8 pf[kQG];
+        b8 pf[kQG], pl[kQG];                // probabilities (kSplitP: hi and lo)
 #pragma unroll
         for (int qg = 0; qg < kQG; ++qg) {
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) pf[qg][t * 4 + r] = (__bf16)fast_exp2(s[qg][t][r]);
+                for (int r = 0; r < 4; ++r) {
+                    const float p = fast_exp2(s[qg][t][r]);
+                    pf[qg][t * 4 + r] = (__bf16)p;
+                    if constexpr (kSplitP) pl[qg][t * 4 + r] = (__bf16)(p - (float)pf[qg][t * 4 + r]);
+                }
             const b2 ones = {(__bf16)1.0f, (__bf16)1.0f};
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const b2 pp = {pf[qg][2 * j], pf[qg][2 * j + 1]};
                 l[qg] = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, l[qg], false);
+                if constexpr (kSplitP) {
+                    const b2 pq = {pl[qg][2 * j], pl[qg][2 * j + 1]};
+                    l[qg] = __builtin_amdgcn_fdot2_f32_bf16(pq, ones, l[qg], false);
+                }
             }
         }
         // O^T += V^T P^T.  V^T fragment of e-block eb: lane (g, i) needs
@@ -293,21 +323,24 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
         // transposing read addresses row 4g + s/4 (+16), dims 16eb + 4(s%4).
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-        for (int eb = 0; eb < 4; ++eb) {
+        for (int eb = 0; eb < kEB; ++eb) {
             b8 vf;
 #pragma unroll
             for (int hh = 0; hh < 2; ++hh) {
                 const int row = kb + 16 * hh + 4 * g + (l16 >> 2);
                 const int ch = 2 * eb + ((l16 & 3) >> 1);
-                const bf16* p = &cV[row * kD + ((ch ^ key_v(row)) << 3) + ((l16 & 1) << 2)];
+                const bf16* p = &cV[row * kD + ((ch ^ key_v<kD>(row)) << 3) + ((l16 & 1) << 2)];
                 const b4v v4 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
                     (__attribute__((address_space(3))) b4v*)(p));
 #pragma unroll
                 for (int j = 0; j < 4; ++j) vf[4 * hh + j] = v4[j];
             }
 #pragma unroll
-            for (int qg = 0; qg < kQG; ++qg)
+            for (int qg = 0; qg < kQG; ++qg) {
                 o[qg][eb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[qg], o[qg][eb], 0, 0, 0);
+                if constexpr (kSplitP)
+                    o[qg][eb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pl[qg], o[qg][eb], 0, 0, 0);
+            }
         }
         __builtin_amdgcn_s_setprio(0);
     };
@@ -316,7 +349,9 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
         if (st + 1 < nst) issue_loads(nK, nV, st + 1);
         const int k0 = st * kKS;
         sub_block(cK, cV, 0, k0);
-        if (k0 + 32 < nkeys) sub_block(cK, cV, 32, k0 + 32);
+#pragma unroll
+        for (int kb = 32; kb < kKS; kb += 32)
+            if (k0 + kb < nkeys) sub_block(cK, cV, kb, k0 + kb);
         __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0): next stage landed
         __syncthreads();
     };
@@ -346,7 +381,7 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
     for (int qg = 0; qg < kQG; ++qg) {
         bad |= nonfinite(l[qg]);
 #pragma unroll
-        for (int eb = 0; eb < 4; ++eb)
+        for (int eb = 0; eb < kEB; ++eb)
 #pragma unroll
             for (int r = 0; r < 4; ++r) bad |= nonfinite(o[qg][eb][r]);
     }
@@ -359,16 +394,17 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
             __builtin_amdgcn_s_waitcnt(0x0F70);
             __syncthreads();
             for (int kb = 0; kb < kKS && st * kKS + kb < nkeys; kb += 16) {
-                b8 kf[2];
+                b8 kf[kES];
                 const int row = kb + l16;
 #pragma unroll
-                for (int es = 0; es < 2; ++es)
-                    kf[es] = *reinterpret_cast<const b8*>(&sK0[row * kD + (((es * 4 + g) ^ key_k(row)) << 3)]);
+                for (int es = 0; es < kES; ++es)
+                    kf[es] = *reinterpret_cast<const b8*>(&sK0[row * kD + (((es * 4 + g) ^ key_k<kD>(row)) << 3)]);
 #pragma unroll
                 for (int qg = 0; qg < kQG; ++qg) {
                     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[0], qf[qg][0], acc, 0, 0, 0);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[1], qf[qg][1], acc, 0, 0, 0);
+#pragma unroll
+                    for (int es = 0; es < kES; ++es)
+                        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[es], qf[qg][es], acc, 0, 0, 0);
                     float mx = -INFINITY;
 #pragma unroll
                     for (int r = 0; r < 4; ++r) {
@@ -395,7 +431,7 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
             if (qi >= kc) continue;
             f16* op = static_cast<f16*>(out) + orow * d + h * kD;
 #pragma unroll
-            for (int eb = 0; eb < 4; ++eb) {
+            for (int eb = 0; eb < kEB; ++eb) {
                 typedef __attribute__((ext_vector_type(4))) _Float16 h4;
                 h4 v;
 #pragma unroll
@@ -409,7 +445,7 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
             // spread over the query's four lanes.
             float am[2] = {0.f, 0.f};
 #pragma unroll
-            for (int eb = 0; eb < 4; ++eb)
+            for (int eb = 0; eb < kEB; ++eb)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     o[qg][eb][r] = keep_f32(o[qg][eb][r] * inv);
@@ -421,7 +457,7 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
             const int e[2] = {mx_block_exp(am[0]), mx_block_exp(am[1])};
             uint8_t* cp = static_cast<uint8_t*>(out) + orow * d + h * kD;
 #pragma unroll
-            for (int eb = 0; eb < 4; ++eb) {
+            for (int eb = 0; eb < kEB; ++eb) {
                 const float sc = mx_inv_scale(e[eb >> 1]);
                 *reinterpret_cast<uint32_t*>(cp + eb * 16 + 4 * g) =
                     mx_pack4(o[qg][eb][0] * sc, o[qg][eb][1] * sc, o[qg][eb][2] * sc, o[qg][eb][3] * sc);
@@ -574,24 +610,34 @@ static int force_exact_flag() {
     return e != nullptr && e[0] == '1';
 }
 
+template <int kD>
+static void launch_rank(const bf16* qkv, f16* o, int64_t row0, int H, const int4* w, int64_t items, int tile,
+                        const bf16* cache_k, const bf16* cache_v, int64_t cache_cap, hipStream_t s) {
+    const int64_t ld = (int64_t)3 * H * kD;
+    if (tile == kLongRankAttnTile)
+        k_attn_mfma<false, kRankQG, false, 8, kD><<<(unsigned)items, 512, 0, s>>>(
+            qkv, ld, o, nullptr, row0, H, w, cache_k, cache_v, cache_cap, force_exact_flag());
+    else if (tile == kRankAttnTile)
+        k_attn_mfma<false, kRankQG, false, 4, kD><<<(unsigned)items, 256, 0, s>>>(
+            qkv, ld, o, nullptr, row0, H, w, cache_k, cache_v, cache_cap, force_exact_flag());
+    else
+        k_attn_mfma<false, kSmallRankQG, false, 4, kD><<<(unsigned)items, 256, 0, s>>>(
+            qkv, ld, o, nullptr, row0, H, w, cache_k, cache_v, cache_cap, force_exact_flag());
+}
+
 hipError_t launch_attn_rank(const bf16* qkv, f16* o, int64_t row0, int H, int D,
                             const int32_t* work, int64_t items,
                             int tile, const bf16* cache_k, const bf16* cache_v, int64_t cache_cap,
                             hipStream_t s) {
     if (items == 0) return hipSuccess;
-    if (D != kD || (tile != kLongRankAttnTile && tile != kRankAttnTile && tile != kSmallRankAttnTile))
+    if ((D != 64 && D != 32) ||
+        (tile != kLongRankAttnTile && tile != kRankAttnTile && tile != kSmallRankAttnTile))
         return hipErrorInvalidValue;
     const int4* w = reinterpret_cast<const int4*>(work);
-    const int64_t ld = (int64_t)3 * H * kD;
-    if (tile == kLongRankAttnTile)
-        k_attn_mfma<false, kRankQG, false, 8><<<(unsigned)items, 512, 0, s>>>(
-            qkv, ld, o, nullptr, row0, H, w, cache_k, cache_v, cache_cap, force_exact_flag());
-    else if (tile == kRankAttnTile)
-        k_attn_mfma<false, kRankQG><<<(unsigned)items, 256, 0, s>>>(
-            qkv, ld, o, nullptr, row0, H, w, cache_k, cache_v, cache_cap, force_exact_flag());
+    if (D == 64)
+        launch_rank<64>(qkv, o, row0, H, w, items, tile, cache_k, cache_v, cache_cap, s);
     else
-        k_attn_mfma<false, kSmallRankQG><<<(unsigned)items, 256, 0, s>>>(
-            qkv, ld, o, nullptr, row0, H, w, cache_k, cache_v, cache_cap, force_exact_flag());
+        launch_rank<32>(qkv, o, row0, H, w, items, tile, cache_k, cache_v, cache_cap, s);
     return hipGetLastError();
 }
 
@@ -600,11 +646,11 @@ hipError_t launch_attn_rank_mx(const bf16* qkv, uint8_t* codes, uint8_t* scales,
                                int64_t items, int tile, const bf16* cache_k, const bf16* cache_v,
                                int64_t cache_cap, hipStream_t s) {
     if (items == 0) return hipSuccess;
-    if (D != kD || (tile != kLongRankAttnTile && tile != kRankAttnTile && tile != kSmallRankAttnTile) ||
+    if (D != 64 || (tile != kLongRankAttnTile && tile != kRankAttnTile && tile != kSmallRankAttnTile) ||
         scales == nullptr)
         return hipErrorInvalidValue;
     const int4* w = reinterpret_cast<const int4*>(work);
-    const int64_t ld = (int64_t)3 * H * kD;
+    const int64_t ld = (int64_t)3 * H * D;
     if (tile == kLongRankAttnTile)
         k_attn_mfma<false, kRankQG, true, 8><<<(unsigned)items, 512, 0, s>>>(
             qkv, ld, codes, scales, row0, H, w, cache_k, cache_v, cache_cap, force_exact_flag());
@@ -622,10 +668,14 @@ hipError_t launch_attn_encode(const bf16* q, f16* o, int64_t row0, int H, int D,
                               int tile, const bf16* cache_k, const bf16* cache_v,
                               int64_t cache_cap, hipStream_t s) {
     if (items == 0) return hipSuccess;
-    if (D != kD || tile != kAttnTile) return hipErrorInvalidValue;
-    k_attn_mfma<true, kEncodeQG><<<(unsigned)items, 256, 0, s>>>(
-        q, (int64_t)H * kD, o, nullptr, row0, H, reinterpret_cast<const int4*>(work), cache_k,
-        cache_v, cache_cap, force_exact_flag());
+    if ((D != 64 && D != 32) || tile != kAttnTile) return hipErrorInvalidValue;
+    const int4* w = reinterpret_cast<const int4*>(work);
+    if (D == 64)
+        k_attn_mfma<true, kEncodeQG><<<(unsigned)items, 256, 0, s>>>(
+            q, (int64_t)H * D, o, nullptr, row0, H, w, cache_k, cache_v, cache_cap, force_exact_flag());
+    else
+        k_attn_mfma<true, kEncodeQG, false, 4, 32><<<(unsigned)items, 256, 0, s>>>(
+            q, (int64_t)H * D, o, nullptr, row0, H, w, cache_k, cache_v, cache_cap, force_exact_flag());
     return hipGetLastError();
 }
 

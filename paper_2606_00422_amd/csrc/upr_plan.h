@@ -23,7 +23,6 @@ constexpr int64_t kSmallRankItems = 512;    // fewer 128-candidate items than th
 // workgroup: each K/V stage then serves twice the queries.
 constexpr int kLongRankAttnTile = 256;
 constexpr double kLongHistory = 4096.0;
-constexpr bool kHaveMfmaAttn = true;
 
 struct EncodePlan {
     int64_t row0 = 0, rows = 0;
@@ -56,8 +55,12 @@ inline int64_t attn_items(const upr_config& c, int U, const int32_t* offs, int t
     return items * c.n_heads;
 }
 
-inline bool use_mfma_attn(const upr_config& c) {
-    return kHaveMfmaAttn && bf16_storage(c) && c.head_dim == 64;
+// Both head_dims of bf16 models run on the matrix cores, except that the fp8
+// variant's ranking pass does so at 64 only (its encoder of the attention
+// output covers whole 64-value heads; at 32 the fallback writes fp32 for the
+// device encoder).
+inline bool use_mfma_attn(const upr_config& c, bool rank) {
+    return bf16_storage(c) && (c.head_dim == 64 || !rank || c.dtype != UPR_BF16_MXFP8);
 }
 
 // Workspace of encode for the history rows of `hoffs` (host offsets): fp32
@@ -69,7 +72,7 @@ inline EncodePlan plan_encode(const upr_config& c, int U, const int32_t* hoffs) 
     p.rows = (int64_t)hoffs[U] - hoffs[0];
     if (p.rows <= 0) { p.rows = 0; return p; }
     const size_t es = dtype_bytes(c), R = (size_t)p.rows, d = c.d_model, F = c.d_ff;
-    p.use_mfma_attn = use_mfma_attn(c);
+    p.use_mfma_attn = use_mfma_attn(c, false);
     if (p.use_mfma_attn) p.work_items = attn_items(c, U, hoffs, p.attn_tile);
     size_t o = 0;
     p.off_g = o; o = align256(o + R * d * 4);
@@ -96,7 +99,7 @@ inline RankPlan plan_rank(const upr_config& c, int U, const int32_t* coffs, cons
     p.rows = (int64_t)coffs[U] - coffs[0];
     if (p.rows <= 0) { p.rows = 0; return p; }
     const size_t es = dtype_bytes(c), R = (size_t)p.rows, d = c.d_model, F = c.d_ff;
-    p.use_mfma_attn = use_mfma_attn(c);
+    p.use_mfma_attn = use_mfma_attn(c, true);
     if (p.use_mfma_attn) {
         double seen = 0.0;                  // history rows seen, summed over candidates
         for (int u = 0; u < U; ++u)
@@ -167,7 +170,7 @@ hipError_t launch_attn_worklist(const int32_t* row_offsets, const int32_t* hist_
                                 int H, int tile, bool reverse, int32_t* work, int64_t items,
                                 int64_t row_first, int64_t row_last, int64_t cap, hipStream_t s);
 
-// MFMA ranking attention (bf16 q|k|v rows and cache, head_dim 64), fp16 output.
+// MFMA ranking attention (bf16 q|k|v rows and cache, head_dim 64 or 32), fp16 output.
 hipError_t launch_attn_rank(const bf16* qkv, f16* o, int64_t row0, int H, int D,
                             const int32_t* work, int64_t items,
                             int tile, const bf16* cache_k, const bf16* cache_v, int64_t cache_cap,
@@ -181,7 +184,7 @@ hipError_t launch_attn_rank_mx(const bf16* qkv, uint8_t* codes, uint8_t* scales,
                                int64_t items, int tile, const bf16* cache_k, const bf16* cache_v,
                                int64_t cache_cap, hipStream_t s);
 
-// MFMA causal encode attention (bf16 query rows and cache, head_dim 64),
+// MFMA causal encode attention (bf16 query rows and cache, head_dim 64 or 32),
 // fp16 output.
 hipError_t launch_attn_encode(const bf16* q, f16* o, int64_t row0, int H, int D,
                               const int32_t* work, int64_t items,

@@ -146,7 +146,7 @@ __device__ __forceinline__ void store_tile(const f32x16 (&acc)[kTN][kTM], char* 
             const_cast<unsigned short*>(static_cast<const unsigned short*>(epi.resid_src)) + wrow0 * epi.ldr,
             (short)0, (int)(rows_valid * epi.ldr * 2), 0x00020000);
         const bool from_src = epi.resid_src != nullptr;
-        const bool acc_has_resid = (MODE == EPI_RESID_LN || MODE == EPI_RESID_SCORE) && epi.acc_resid != 0;
+        const bool acc_has_resid = MODE != EPI_RESID_LN_MX && epi.acc_resid != 0;
         auto load_resid = [&](int i, float4 (&dst)[8]) {
             if (acc_has_resid) return;          // the accumulators carry it
             if (from_src) {

@@ -187,8 +187,8 @@ __global__ __launch_bounds__(kThreads, 1) void k_gemm_mfma(const void* __restric
         for (int i = 0; i < kTM; ++i)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[j][i][r] = 0.f;
-    // (FFN down with its LayerNorm: the accumulators start at the residual)
-    if constexpr (!MX && (MODE == EPI_RESID_LN || MODE == EPI_RESID_SCORE))
+    // (FFN down before a LayerNorm: the accumulators start at the residual)
+    if constexpr (!MX && (MODE == EPI_RESID || MODE == EPI_RESID_LN || MODE == EPI_RESID_SCORE))
         if (epi.acc_resid) load_acc_resid<kTM>(acc, epi, m0 + wm * kWM, n0 + wn * kWN, M, N, lane);
 
     const int lrow = lane & 31, lhalf = lane >> 5;
@@ -488,10 +488,51 @@ hipError_t launch_gemm_mx(const uint8_t* A, const uint8_t* A_scales, const uint8
     }
 }
 
-// bf16 models: fp16 projection operands on the matrix cores
+// Whether a residual update runs on small tiles with its LayerNorm (or score
+// head) as a launch of its own, instead of on whole-row tiles with it in the
+// epilogue.  Whole-row tiles are few and walk K with nobody beside them.  FFN
+// down (K > N): until 128-row tiles fill the device (2000 rows x 512, K 2048:
+// 29 us against 11.2 + 3.3; 16000 rows: 91 against 43 + 9.6).  O projection:
+// while the 64 x 64 tiles all run at once (2000 rows, K 512: 11.7 against
+// 5.6 + 3.3; 8000 rows: 15 against 11.7 + 5.9).
+bool separate_layernorm(int64_t M, int N, int K) {
+    const int64_t cus = gemm_detail::device_cus();
+    if (K > N) return (M + 127) / 128 < cus;
+    return ((M + 63) / 64) * (int64_t)((N + 63) / 64) <= 2 * cus;
+}
+
+// bf16 models: fp16 projection operands on the matrix cores.  Which tile is
+// fastest depends on how its count fills the device (every choice gives the
+// same bits); us per launch at the lines, d 512 unless said:
+//  * 64 x 64 tiles while they all run at once, two to a compute unit (4000
+//    rows x 512, K 512, 504 tiles: 7.5 against 9.5 on 64 x 256 tiles; at
+//    1000 tiles 12.2 against 11.7);
+//  * 256 x 256 tiles (k_gemm_mfma) once they fill the device, unless the
+//    last of their waves of tiles is so empty that 128 x 128 tiles, which
+//    run at 80-85% of their rate when full, lose less (16000 x 1536: 378
+//    tiles, 36 against 34; 8000 x 2048: 256 tiles, 22 against 26).  The
+//    residual update keeps them whatever the fill (30000 x 768, K 768: 61
+//    against 67: its epilogue overlaps the next MFMAs);
+//  * between the two 128 x 128 tiles as soon as some compute units get two
+//    (8000 x 1536, 756 tiles: 20 against 25), else 64 x 256 tiles (8000 x
+//    512, K 2048, 252 tiles of 128: 26 against 32).
 template <>
 hipError_t launch_gemm<f16, bf16>(const f16* A, int64_t lda, const f16* W, int64_t M, int N,
                                   int K, const Epilogue& epi, hipStream_t s) {
+    const int64_t cus = gemm_detail::device_cus();
+    const bool whole_rows = epi.mode == EPI_RESID_LN || epi.mode == EPI_RESID_SCORE;
+    if (!whole_rows) {
+        auto tiles = [&](int b) { return ((M + b - 1) / b) * (int64_t)((N + b - 1) / b); };
+        auto fill = [](int64_t n, int64_t slots) { return (double)n / (double)((n + slots - 1) / slots * slots); };
+        int block = 0;
+        if (tiles(64) <= 2 * cus)
+            block = 64;
+        else if (tiles(256) >= cus)
+            block = epi.mode != EPI_RESID && fill(tiles(256), cus) < 0.8 * fill(tiles(128), 2 * cus) ? 128 : 0;
+        else if (tiles(128) > cus)
+            block = 128;
+        if (block != 0) return launch_gemm_small<f16, bf16>(A, lda, W, M, N, K, epi, block, s);
+    }
     return launch_gemm_mfma(A, lda, W, M, N, K, epi, s);
 }
 

@@ -266,6 +266,102 @@ __global__ __launch_bounds__(256) void k_score_head(const float* __restrict__ g,
     if (lane == 0) scores[row] = acc + b[0];
 }
 
+// LayerNorm (fp16 output) or, with `scores`, the score head of fp32 rows of at
+// most 512 values in the association tree of the GEMMs' whole-row epilogue
+// (EPI_RESID_LN, EPI_RESID_SCORE), so that a residual update on small tiles
+// followed by this kernel gives the bits of that epilogue: statistics per
+// 64-column block over 16 lanes of four columns (exchanges 8, 4, 2, 1 apart),
+// then the blocks in order (Chan et al.'s pairwise update).
+template <bool SCORE>
+__global__ __launch_bounds__(256) void k_block_layernorm(const float* __restrict__ g, f16* __restrict__ a,
+                                                         int64_t rows, int d, const float* __restrict__ gain,
+                                                         const float* __restrict__ shift, float eps,
+                                                         const float* __restrict__ w,
+                                                         const float* __restrict__ b,
+                                                         float* __restrict__ scores) {
+    const int64_t row = (int64_t)blockIdx.x * kRowsPerBlock + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (row >= rows) return;
+    auto row16_sum = [](float t) {
+        t += __shfl_xor(t, 8, 64);
+        t += __shfl_xor(t, 4, 64);
+        t += __shfl_xor(t, 2, 64);
+        return t + __shfl_xor(t, 1, 64);
+    };
+    // lane l holds columns 256j + 4l .. +3, of block 4j + l / 16
+    float4 h[2], gq[2], bq[2], wq[2];
+    bool on[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int c = 256 * j + 4 * lane;
+        on[j] = c < d;
+        h[j] = gq[j] = bq[j] = wq[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (on[j]) {
+            h[j] = *reinterpret_cast<const float4*>(g + row * d + c);
+            gq[j] = *reinterpret_cast<const float4*>(gain + c);
+            bq[j] = *reinterpret_cast<const float4*>(shift + c);
+            if constexpr (SCORE) wq[j] = *reinterpret_cast<const float4*>(w + c);
+        }
+    }
+    float mean[2], m2[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        mean[j] = row16_sum((h[j].x + h[j].y) + (h[j].z + h[j].w)) / 64.0f;
+        const float u0 = h[j].x - mean[j], u1 = h[j].y - mean[j], u2 = h[j].z - mean[j], u3 = h[j].w - mean[j];
+        m2[j] = row16_sum(fmaf(u0, u0, fmaf(u1, u1, fmaf(u2, u2, u3 * u3))));
+    }
+    const int blocks = d >> 6;
+    float mean_w[8], m2_w[8], tot = 0.f, sum = 0.f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        mean_w[k] = __shfl(mean[k >> 2], 16 * (k & 3), 64);
+        m2_w[k] = __shfl(m2[k >> 2], 16 * (k & 3), 64);
+        if (k < blocks) {
+            tot += 64.0f;
+            sum = fmaf(64.0f, mean_w[k], sum);
+        }
+    }
+    const float mu = sum / tot;
+    float M2 = 0.f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+        if (k < blocks) {
+            const float dm = mean_w[k] - mu;
+            M2 += fmaf(64.0f * dm, dm, m2_w[k]);
+        }
+    const float rstd = 1.0f / sqrtf(M2 / tot + eps);
+    if constexpr (SCORE) {
+        float part[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            float d4 = 0.f;
+            if (on[j]) {
+                d4 = fmaf(fmaf((h[j].x - mu) * rstd, gq[j].x, bq[j].x), wq[j].x, d4);
+                d4 = fmaf(fmaf((h[j].y - mu) * rstd, gq[j].y, bq[j].y), wq[j].y, d4);
+                d4 = fmaf(fmaf((h[j].z - mu) * rstd, gq[j].z, bq[j].z), wq[j].z, d4);
+                d4 = fmaf(fmaf((h[j].w - mu) * rstd, gq[j].w, bq[j].w), wq[j].w, d4);
+            }
+            part[j] = row16_sum(d4);
+        }
+        float sc = __shfl(part[0], 0, 64);
+#pragma unroll
+        for (int k = 1; k < 8; ++k) sc += __shfl(part[k >> 2], 16 * (k & 3), 64);
+        if (lane == 0) scores[row] = sc + b[0];
+    } else {
+        typedef __attribute__((ext_vector_type(4))) _Float16 h4;
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+            if (on[j]) {
+                h4 o;
+                o[0] = (f16)keep_f32(fmaf((h[j].x - mu) * rstd, gq[j].x, bq[j].x));
+                o[1] = (f16)keep_f32(fmaf((h[j].y - mu) * rstd, gq[j].y, bq[j].y));
+                o[2] = (f16)keep_f32(fmaf((h[j].z - mu) * rstd, gq[j].z, bq[j].z));
+                o[3] = (f16)keep_f32(fmaf((h[j].w - mu) * rstd, gq[j].w, bq[j].w));
+                *reinterpret_cast<h4*>(a + row * d + 256 * j + 4 * lane) = o;
+            }
+    }
+}
+
 inline unsigned grid_rows(int64_t rows) {
     return (unsigned)((rows + kRowsPerBlock - 1) / kRowsPerBlock);
 }
@@ -327,6 +423,20 @@ hipError_t launch_score_head(const float* g, float* scores, int64_t rows, int d,
     else
         k_score_head<false><<<grid_rows(rows), 256, 0, s>>>(g, scores, rows, d, fw.lnf_g,
                                                             fw.lnf_b, fw.w_score, fw.b_score, eps);
+    return hipGetLastError();
+}
+
+hipError_t launch_block_layernorm(const float* g, f16* a, int64_t rows, int d, const float* gain,
+                                  const float* shift, float eps, const FinalWeights* fw, float* scores,
+                                  hipStream_t s) {
+    if (rows == 0) return hipSuccess;
+    if (d % 64 != 0 || d > kResidLnMaxN) return hipErrorInvalidValue;
+    if (scores != nullptr)
+        k_block_layernorm<true><<<grid_rows(rows), 256, 0, s>>>(g, nullptr, rows, d, gain, shift, eps,
+                                                               fw->w_score, fw->b_score, scores);
+    else
+        k_block_layernorm<false><<<grid_rows(rows), 256, 0, s>>>(g, a, rows, d, gain, shift, eps, nullptr,
+                                                                nullptr, nullptr);
     return hipGetLastError();
 }
 

@@ -1,11 +1,9 @@
-// Plain kernels: a tiled FMA GEMM with the projection epilogues, and
-// per-(row, head) attention for ranking and for history encoding.  They run
-// the fp32 models (all arithmetic fp32) and the shapes the MFMA kernels do
-// not take (head_dim 32).  Like every kernel here they are tested against
+// Plain kernels: per-(row, head) attention for ranking and for history
+// encoding.  They run the fp32 models (all arithmetic fp32) and the shapes the
+// MFMA kernels do not take.  Like every kernel here they are tested against
 // the CPU oracle.
 #include <cmath>
 
-#include "epilogue.h"
 #include "upr_internal.h"
 #include "upr_plan.h"
 
@@ -24,55 +22,6 @@ __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) v = fmaxf(v, __shfl_xor(v, m, 64));
     return v;
-}
-
-// ---------------------------------------------------------------------------
-// GEMM: 64x64 output tile per 256-thread block, K in steps of 16 through LDS,
-// each thread a 4x4 register tile.
-// ---------------------------------------------------------------------------
-template <typename TA, typename TKV>
-__global__ __launch_bounds__(256) void k_gemm_simple(const TA* __restrict__ A, int64_t lda,
-                                                     const TA* __restrict__ W, int64_t M, int N,
-                                                     int K, Epilogue epi) {
-    __shared__ float As[16][68];
-    __shared__ float Ws[16][68];
-    const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-    const int64_t m0 = (int64_t)blockIdx.y * 64;
-    const int n0 = blockIdx.x * 64;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += 16) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int idx = threadIdx.x + 256 * i;
-            const int r = idx >> 4, kk = idx & 15;
-            const int64_t gm = m0 + r;
-            const int gn = n0 + r, gk = k0 + kk;
-            As[kk][r] = (gm < M && gk < K) ? to_f(A[gm * lda + gk]) : 0.f;
-            Ws[kk][r] = (gn < N && gk < K) ? to_f(W[(int64_t)gn * K + gk]) : 0.f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) a[i] = As[kk][ty + 16 * i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) b[j] = Ws[kk][tx + 16 * j];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int64_t m = m0 + ty + 16 * i;
-            const int n = n0 + tx + 16 * j;
-            if (m < M && n < N) epilogue_apply<TKV, TA>(epi, m, n, acc[i][j]);
-        }
 }
 
 // Index of the segment holding absolute row `row`: the largest u in [0, U)
@@ -207,15 +156,6 @@ __global__ __launch_bounds__(256) void k_attn_encode_simple(
 
 }  // namespace
 
-template <typename TA, typename TKV>
-hipError_t launch_gemm_simple(const TA* A, int64_t lda, const TA* W, int64_t M, int N, int K,
-                              const Epilogue& epi, hipStream_t s) {
-    if (M == 0) return hipSuccess;
-    dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64));
-    k_gemm_simple<TA, TKV><<<grid, 256, 0, s>>>(A, lda, W, M, N, K, epi);
-    return hipGetLastError();
-}
-
 template <typename TKV, typename TA>
 hipError_t launch_attn_rank_simple(const TKV* qkv, TA* o, int64_t rows, int64_t row0, int H,
                                    int D, const int32_t* cand_offsets,
@@ -253,8 +193,6 @@ hipError_t launch_attn_encode_simple(const TKV* q, TA* o, int64_t rows, int64_t 
 }
 
 #define UPR_INST(TKV, TA)                                                                       \
-    template hipError_t launch_gemm_simple<TA, TKV>(const TA*, int64_t, const TA*, int64_t, int, \
-                                                    int, const Epilogue&, hipStream_t);         \
     template hipError_t launch_attn_rank_simple<TKV, TA>(                                      \
         const TKV*, TA*, int64_t, int64_t, int, int, const int32_t*, const int32_t*, int,       \
         const TKV*, const TKV*, int64_t, hipStream_t);                                          \
@@ -265,14 +203,6 @@ hipError_t launch_attn_encode_simple(const TKV* q, TA* o, int64_t rows, int64_t 
 UPR_INST(float, float)
 UPR_INST(bf16, f16)
 #undef UPR_INST
-// fp32 models: every projection runs on the FMA GEMM (fp32 residual rows only)
-template <>
-hipError_t launch_gemm<float, float>(const float* A, int64_t lda, const float* W, int64_t M,
-                                     int N, int K, const Epilogue& epi, hipStream_t s) {
-    if (epi.resid_src != nullptr) return hipErrorInvalidValue;
-    return launch_gemm_simple<float, float>(A, lda, W, M, N, K, epi, s);
-}
-
 // the fp8 projection variant's fallback attention: bf16 queries/keys/values
 // and cache, fp32 output for the MXFP8 encoder
 template hipError_t launch_attn_rank_simple<bf16, float>(const bf16*, float*, int64_t, int64_t,

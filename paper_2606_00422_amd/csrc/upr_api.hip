@@ -437,10 +437,13 @@ static bool fused_layernorm(const upr_config& c) {
 // written and the O projection reads the residual from these token rows.
 // scores (last ranking layer, fused LayerNorms): FFN down ends in the score
 // head, scores[m] = LN_f(g[m]) . w + b with score_fin, and g is left stale.
+// In calls too small for whole-row tiles (separate_layernorm) the LayerNorms
+// and the score head are launches of their own, in the epilogues' summation
+// order: the same bits.
 // Timing scopes are named "<stage>.gemm_o" etc.; the one-kernel tail is
 // "<stage>.oproj_ffn".
 template <typename Types>
-static hipError_t launch_ffn_block(const char* const names[5], const upr_config& c,
+static hipError_t launch_ffn_block(const char* const names[7], const upr_config& c,
                                    const LayerWeights& w, const typename Types::act* o,
                                    typename Types::act* a, typename Types::act* h, float* g,
                                    int64_t R, const float* next_g, const float* next_b,
@@ -469,7 +472,9 @@ static hipError_t launch_ffn_block(const char* const names[5], const upr_config&
     // head) for calls whose 128-row tiles fill the device
     const bool tail = std::is_same_v<Types, Bf16Types> && fuse && w.WoP != nullptr && w.W1p != nullptr &&
                       (next_g != nullptr || scores != nullptr) && ffn_fused_rows(R);
+    const bool sep_o = fuse && !tail && separate_layernorm(R, d, d);
     if (!tail) {
+        if (sep_o) r.mode = EPI_RESID;
         ProfScope ps(names[0], s);
         e = launch_gemm<TA, T>(o, d, static_cast<const TA*>(w.Wo), R, d, d, r, s);
     }
@@ -479,6 +484,13 @@ static hipError_t launch_ffn_block(const char* const names[5], const upr_config&
         e = launch_layernorm<TA>(g, a, R, d, w.ln2_g, w.ln2_b, eps, s);
     }
     if (e != hipSuccess) return e;
+    if constexpr (std::is_same_v<Types, Bf16Types>) {
+        if (sep_o) {
+            ProfScope ps(names[1], s);
+            e = launch_block_layernorm(g, a, R, d, w.ln2_g, w.ln2_b, eps, nullptr, nullptr, s);
+            if (e != hipSuccess) return e;
+        }
+    }
     if constexpr (std::is_same_v<Types, Bf16Types>) {
         if (tail) {
             const Epilogue oproj = r;
@@ -531,14 +543,25 @@ static hipError_t launch_ffn_block(const char* const names[5], const upr_config&
     // FFN down with its LayerNorm or score head accumulates onto the
     // residual (the fused tail's arithmetic, so both give the same bits)
     r.acc_resid = std::is_same_v<Types, Bf16Types> && (r.mode == EPI_RESID_LN || r.mode == EPI_RESID_SCORE);
-    ProfScope ps(names[3], s);
-    return launch_gemm<TA, T>(h, F, static_cast<const TA*>(w.W2), R, d, F, r, s);
+    const bool sep_d = r.acc_resid && separate_layernorm(R, d, F);
+    if (sep_d) r.mode = EPI_RESID;
+    {
+        ProfScope ps(names[3], s);
+        e = launch_gemm<TA, T>(h, F, static_cast<const TA*>(w.W2), R, d, F, r, s);
+    }
+    if constexpr (std::is_same_v<Types, Bf16Types>) {
+        if (e == hipSuccess && sep_d) {
+            ProfScope ps(scores != nullptr ? names[6] : names[5], s);
+            e = launch_block_layernorm(g, a, R, d, next_g, next_b, eps, score_fin, scores, s);
+        }
+    }
+    return e;
 }
 
-static const char* const kEncodeFfnNames[5] = {"encode.gemm_o", "encode.ln2", "encode.gemm_up",
-                                               "encode.gemm_down", "encode.oproj_ffn"};
-static const char* const kRankFfnNames[5] = {"rank.gemm_o", "rank.ln2", "rank.gemm_up",
-                                             "rank.gemm_down", "rank.oproj_ffn"};
+static const char* const kEncodeFfnNames[7] = {"encode.gemm_o", "encode.ln2", "encode.gemm_up",
+                                               "encode.gemm_down", "encode.oproj_ffn", "encode.ln1", ""};
+static const char* const kRankFfnNames[7] = {"rank.gemm_o", "rank.ln2", "rank.gemm_up", "rank.gemm_down",
+                                             "rank.oproj_ffn", "rank.ln1", "rank.score_head"};
 
 template <typename Types>
 static upr_status run_encode(const upr_model* m, const typename Types::kv* hist_emb,

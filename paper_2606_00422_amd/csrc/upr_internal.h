@@ -147,8 +147,8 @@ struct Epilogue {
     // (leading dimension ldr) instead of resid, and the sum still goes to
     // resid: the first layer's update reads the tokens themselves
     const void* resid_src;
-    // EPI_RESID_LN / EPI_RESID_SCORE with fp16 operands: nonzero when the
-    // accumulators start at resid / acc_scale instead of zero (acc_scale a
+    // EPI_RESID / EPI_RESID_LN / EPI_RESID_SCORE with fp16 operands: nonzero
+    // when the accumulators start at resid / acc_scale instead of zero (acc_scale a
     // power of two, so the division is exact).  The update is then
     // acc * acc_scale + bias, with no residual read in the epilogue: the FFN
     // down accumulates onto the residual that the O projection produced.
@@ -170,6 +170,12 @@ hipError_t launch_init_layernorm(const TKV* x, float* g, TA* a, int64_t rows, in
 template <typename TA>
 hipError_t launch_layernorm(const float* g, TA* a, int64_t rows, int d, const float* gain,
                             const float* shift, float eps, hipStream_t s);
+// LN(g) -> a, or with `scores` the score head (weights of fw), in the
+// summation order of the GEMMs' whole-row epilogues (EPI_RESID_LN,
+// EPI_RESID_SCORE): bit for bit what they write.  d a multiple of 64, <= 512.
+hipError_t launch_block_layernorm(const float* g, f16* a, int64_t rows, int d, const float* gain,
+                                  const float* shift, float eps, const FinalWeights* fw, float* scores,
+                                  hipStream_t s);
 hipError_t launch_score_head(const float* g, float* scores, int64_t rows, int d,
                              const FinalWeights& fw, float eps, hipStream_t s);
 
@@ -195,12 +201,6 @@ hipError_t launch_mx_quantize(const T* x, int64_t rows, int k, uint8_t* codes, u
 hipError_t launch_gemm_mx(const uint8_t* A, const uint8_t* A_scales, const uint8_t* W,
                           const uint8_t* W_scales, int64_t M, int N, int K, const Epilogue& epi,
                           hipStream_t s);
-
-// Reference-quality GEMM: out = A[M,K] W[N,K]^T + epilogue; A and W are of the
-// projection operand type TA, kv-typed epilogue outputs of type TKV.
-template <typename TA, typename TKV>
-hipError_t launch_gemm_simple(const TA* A, int64_t lda, const TA* W, int64_t M, int N, int K,
-                              const Epilogue& epi, hipStream_t s);
 
 // Reference-quality attention.  qkv / q rows are relative to the call's first
 // row `row0`; offsets are absolute.  Logits use exp2 with queries pre-scaled by

@@ -130,8 +130,8 @@ inline RankPlan plan_rank(const upr_config& c, int U, const int32_t* coffs, cons
     return p;
 }
 
-// Projection GEMM, out = A[M,K] W[N,K]^T + epilogue: fp32 models use the
-// reference FMA kernel, bf16 models the fp16 MFMA kernel.
+// Projection GEMM, out = A[M,K] W[N,K]^T + epilogue, on the tile that fills
+// the device best: fp32 operands (fp32 models) or fp16 (bf16 models).
 template <typename TA, typename TKV>
 hipError_t launch_gemm(const TA* A, int64_t lda, const TA* W, int64_t M, int N, int K,
                        const Epilogue& epi, hipStream_t s);
@@ -140,6 +140,19 @@ hipError_t launch_gemm(const TA* A, int64_t lda, const TA* W, int64_t M, int N, 
 // GEMM, launch_gemm_mx, is declared with the other launchers.)
 hipError_t launch_gemm_mfma(const f16* A, int64_t lda, const f16* W, int64_t M, int N, int K,
                             const Epilogue& epi, hipStream_t s);
+
+// Whether a residual update of M rows, [M, K] x [N, K]^T, is followed by a
+// launch_block_layernorm instead of an EPI_RESID_LN / EPI_RESID_SCORE epilogue
+// (same bits either way).
+bool separate_layernorm(int64_t M, int N, int K);
+
+// The same product on block x block tiles (k_gemm_small.hip; 128, or 64 for
+// fp16 and 32 for fp32), modes EPI_STORE, EPI_GELU, EPI_GELU_PERM (fp16),
+// EPI_RESID (acc_resid allowed) and EPI_QKV_CACHE.  A and W fp16 (K a multiple
+// of 64) or fp32 (of 32).
+template <typename TA, typename TKV>
+hipError_t launch_gemm_small(const TA* A, int64_t lda, const TA* W, int64_t M, int N, int K,
+                             const Epilogue& epi, int block, hipStream_t s);
 
 // Fused layer tail (k_ffn_fused.hip) on the fp32 residual g:
 //   g += O Wo^T + bo;  a = LN2(g);  g += gelu(a W1^T + b1) W2^T + b2

@@ -1,0 +1,66 @@
+"""The tile a projection runs on depends on the size of the call and never
+changes a result: the same candidates ranked in calls of 1 to 33,000 rows
+(32-, 64-, 128- and 256-wide tiles, whole-row tiles, the fused tail; with the
+LayerNorms and the score head inside an epilogue or as launches of their own)
+get the same bits, and a sample of them agrees with the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from synth import make_inputs
+
+from .gpu_util import ATOL, GpuRun, assert_scores_match, say
+
+pytestmark = pytest.mark.gpu
+
+# (d, H, L, F, dtype, largest call): K-loops of 1, 2, 5 and 8 steps and their
+# remainders, columns that fill no tile, every LayerNorm width class
+CASES = [
+    (64, 1, 2, 64, "bf16", 20000),
+    (320, 5, 1, 576, "bf16", 20000),        # no fused tail: whole-row tiles
+    (256, 4, 2, 512, "bf16", 33000),        # fused tail in the largest call
+    (512, 8, 1, 1024, "bf16", 33000),
+    (768, 12, 1, 832, "bf16", 9000),        # rows past the whole-row tile
+    (64, 2, 2, 192, "f32", 9000),
+    (320, 5, 1, 448, "f32", 9000),
+]
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_call_size_does_not_change_scores(case):
+    d, H, L, F, dt, top = CASES[case]
+    inp = make_inputs([37], [top], d, H, L, F, dtype=dt, seed=700 + case, variant="perturbed")
+    run = GpuRun(inp)
+    run.encode()
+    run.rank()
+    ref = run.scores_np().copy()
+    assert np.all(np.isfinite(ref))
+    for lo, hi in ((0, 1), (5, 68), (63, 127), (100, 228), (7, 1000), (1000, 3050), (0, 4097), (11, top // 2)):
+        say(f"[gpu] small tiles d={d} F={F} {dt}: rows {lo}..{hi} of {top}")
+        run.scores.fill_(float("nan"))
+        run.rank(coff=np.array([lo, hi], np.int32))
+        got = run.scores_np()
+        assert np.array_equal(got[lo:hi], ref[lo:hi]), f"rows {lo}..{hi}"
+        assert np.all(np.isnan(got[hi:]))
+    rows = np.arange(0, top, max(1, top // 61))
+    o = oracle.rank(inp.weights, d, H, L, F, run.cache_np(), inp.hist_offsets, inp.cand_emb,
+                    inp.cand_offsets, cand_rows=rows)
+    # fp32 models: sums of up to max(d, F) products and a few such layers, at 2^-24 each
+    err = assert_scores_match(ref[rows], o[rows], f"d={d} {dt}", scale=1.0 if dt == "bf16" else 1e-4 / ATOL)
+    say(f"[gpu] small tiles d={d} {dt}: max |score err| {err:.3e}")
+
+
+@pytest.mark.parametrize("dt", ["bf16", "f32"])
+def test_encode_call_size_does_not_change_the_cache(dt):
+    """One user's rows of the cache, encoded alone and among others."""
+    lens = [700, 33, 1, 3000, 130]
+    inp = make_inputs(lens, [1] * len(lens), 256, 4, 2, 512, dtype=dt, seed=720, variant="perturbed")
+    run = GpuRun(inp)
+    run.encode()
+    ref = run.cache_np().copy()
+    ho = inp.hist_offsets
+    for u in range(len(lens)):
+        run.cache.zero_()
+        run.encode(hoff=np.array([ho[u], ho[u + 1]], np.int32))
+        got = run.cache_np()
+        assert np.array_equal(got[:, :, :, ho[u]:ho[u + 1]], ref[:, :, :, ho[u]:ho[u + 1]]), f"user {u}"

@@ -1,7 +1,8 @@
-// Plain kernels: per-(row, head) attention for ranking and for history
-// encoding.  They run the fp32 models (all arithmetic fp32) and the shapes the
-// MFMA kernels do not take.  Like every kernel here they are tested against
-// the CPU oracle.
+// Plain attention, one wave per (row, head), for ranking and for history
+// encoding, in fp32 arithmetic: the fp8 variant's ranking pass at head_dim 32,
+// and, for fp32 models and head_dim 32, calls whose workspace has no room for
+// a work list or whose histories pass the matrix-core kernels' limit.  Like
+// every kernel here they are tested against the CPU oracle.
 #include <cmath>
 
 #include "upr_internal.h"

@@ -228,6 +228,18 @@ upr_status check_workspace(void* ws, size_t ws_bytes, size_t need) {
     return UPR_OK;
 }
 
+// The plan make(true), or make(false), without a work list where one is
+// optional, if only that fits `have` bytes.
+template <typename Make>
+auto fit_plan(const Make& make, size_t have) {
+    auto p = make(true);
+    if (p.bytes > have) {
+        auto q = make(false);
+        if (q.bytes <= have) return q;
+    }
+    return p;
+}
+
 #define UPR_HIP(...)                                                                            \
     do {                                                                                        \
         hipError_t e_ = (__VA_ARGS__);                                                          \
@@ -623,6 +635,12 @@ static upr_status run_encode(const upr_model* m, const typename Types::kv* hist_
                                               cache->capacity_rows, s));
                 done = true;
             }
+        } else if (p.use_mfma_attn) {
+            UPR_LAUNCH("encode.attn",
+                       launch_attn_f32(true, q, o, p.row0, H, D, reinterpret_cast<const int32_t*>(ws + p.off_work),
+                                       p.work_items, static_cast<const T*>(e.cache_k),
+                                       static_cast<const T*>(e.cache_v), cache->capacity_rows, s));
+            done = true;
         }
         if (!done)
             UPR_LAUNCH("encode.attn",
@@ -709,6 +727,11 @@ static upr_status run_rank(const upr_model* m, const upr_kv_cache* cache,
                                          s));
                 done = true;
             }
+        } else if (p.use_mfma_attn) {
+            UPR_LAUNCH("rank.attn",
+                       launch_attn_f32(false, qkv, o, p.row0, H, D, reinterpret_cast<const int32_t*>(ws + p.off_work),
+                                       p.work_items, ck, cv, cache->capacity_rows, s));
+            done = true;
         }
         if (!done)
             UPR_LAUNCH("rank.attn", launch_attn_rank_simple<T, TA>(qkv, o, R, p.row0, H, D, cand->offsets_dev,
@@ -949,7 +972,8 @@ upr_status upr_encode_user(const upr_model* m, const void* hist_emb, const upr_s
     if (cache->capacity_rows < 0 || last > cache->capacity_rows)
         return fail(UPR_ERR_CAPACITY, "history rows end at %lld, cache capacity is %lld",
                     (long long)last, (long long)cache->capacity_rows);
-    const upr::EncodePlan p = upr::plan_encode(m->cfg, hist->num_users, hist->offsets_host);
+    const upr::EncodePlan p = fit_plan(
+        [&](bool lists) { return upr::plan_encode(m->cfg, hist->num_users, hist->offsets_host, lists); }, ws_bytes);
     st = check_workspace(ws, ws_bytes, p.bytes);
     if (st != UPR_OK) return st;
     if (p.rows == 0) return ok();
@@ -989,7 +1013,11 @@ static upr_status rank_entry(const upr_model* m, const upr_kv_cache* cache,
         if (!scores) return fail(UPR_ERR_NULL, "scores is NULL");
         if (hl > hf && !cache->data) return fail(UPR_ERR_NULL, "cache data is NULL");
     }
-    const upr::RankPlan p = upr::plan_rank(m->cfg, cand->num_users, cand->offsets_host, hist->offsets_host);
+    const upr::RankPlan p = fit_plan(
+        [&](bool lists) {
+            return upr::plan_rank(m->cfg, cand->num_users, cand->offsets_host, hist->offsets_host, 0, lists);
+        },
+        scratch ? UPR_NOALLOC_SCRATCH_BYTES : ws_bytes);
     if (scratch) {
         if (p.bytes > UPR_NOALLOC_SCRATCH_BYTES)
             return fail(UPR_ERR_LIMIT, "the call needs a %zu-byte workspace; the no-alloc scratch "
@@ -1140,8 +1168,12 @@ upr_status upr_rank_actions(const upr_model* m, const upr_heads* hd, const upr_k
         if (!cand_emb) return fail(UPR_ERR_NULL, "cand_emb is NULL");
         if (hl > hf && !cache->data) return fail(UPR_ERR_NULL, "cache data is NULL");
     }
-    const upr::RankPlan p = upr::plan_rank(m->cfg, cand->num_users, cand->offsets_host, hist->offsets_host,
-                                           hd->C * hd->Fh);
+    const upr::RankPlan p = fit_plan(
+        [&](bool lists) {
+            return upr::plan_rank(m->cfg, cand->num_users, cand->offsets_host, hist->offsets_host, hd->C * hd->Fh,
+                                  lists);
+        },
+        ws_bytes);
     st = check_workspace(ws, ws_bytes, p.bytes);
     if (st != UPR_OK) return st;
     if (p.rows == 0) return ok();

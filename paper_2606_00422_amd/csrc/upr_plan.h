@@ -23,6 +23,7 @@ constexpr int64_t kSmallRankItems = 512;    // fewer 128-candidate items than th
 // workgroup: each K/V stage then serves twice the queries.
 constexpr int kLongRankAttnTile = 256;
 constexpr double kLongHistory = 4096.0;
+constexpr int kF32AttnTile = 32;            // fp32 models, both passes
 
 struct EncodePlan {
     int64_t row0 = 0, rows = 0;
@@ -55,24 +56,34 @@ inline int64_t attn_items(const upr_config& c, int U, const int32_t* offs, int t
     return items * c.n_heads;
 }
 
-// Both head_dims of bf16 models run on the matrix cores, except that the fp8
-// variant's ranking pass does so at 64 only (its encoder of the attention
-// output covers whole 64-value heads; at 32 the fallback writes fp32 for the
-// device encoder).
-inline bool use_mfma_attn(const upr_config& c, bool rank) {
-    return bf16_storage(c) && (c.head_dim == 64 || !rank || c.dtype != UPR_BF16_MXFP8);
+// Whether the attention runs on the matrix cores, from a work list in the
+// workspace.  bf16 models of head_dim 64 always do.  At head_dim 32, and for
+// fp32 models, a one-wave-per-row kernel that needs no list stands in
+//  * for histories whose keys pass the 2 GB a buffer descriptor spans here,
+//  * for the fp8 variant's ranking pass (head_dim 32: the matrix-core kernel's
+//    MXFP8 output covers whole 64-value heads), and
+//  * where the list does not fit (`lists` false): a workspace that held these
+//    calls before they had a list still does.
+inline bool use_mfma_attn(const upr_config& c, bool rank, int U, const int32_t* hoffs, bool lists) {
+    if (bf16_storage(c) && c.head_dim == 64) return true;
+    if (!lists || (rank && c.dtype == UPR_BF16_MXFP8)) return false;
+    const int64_t most = (int64_t{1} << 31) / (c.head_dim * (int64_t)dtype_bytes(c));
+    for (int u = 0; u < U; ++u)
+        if ((int64_t)hoffs[u + 1] - hoffs[u] >= most) return false;
+    return true;
 }
 
 // Workspace of encode for the history rows of `hoffs` (host offsets): fp32
 // residual stream, then LayerNorm output, queries, attention output and FFN
-// hidden (model dtype), and (bf16 models) the attention work list.
-inline EncodePlan plan_encode(const upr_config& c, int U, const int32_t* hoffs) {
+// hidden (model dtype), and the attention work list.
+inline EncodePlan plan_encode(const upr_config& c, int U, const int32_t* hoffs, bool lists = true) {
     EncodePlan p;
     p.row0 = hoffs[0];
     p.rows = (int64_t)hoffs[U] - hoffs[0];
     if (p.rows <= 0) { p.rows = 0; return p; }
     const size_t es = dtype_bytes(c), R = (size_t)p.rows, d = c.d_model, F = c.d_ff;
-    p.use_mfma_attn = use_mfma_attn(c, false);
+    p.use_mfma_attn = use_mfma_attn(c, false, U, hoffs, lists);
+    if (!bf16_storage(c)) p.attn_tile = kF32AttnTile;
     if (p.use_mfma_attn) p.work_items = attn_items(c, U, hoffs, p.attn_tile);
     size_t o = 0;
     p.off_g = o; o = align256(o + R * d * 4);
@@ -88,19 +99,22 @@ inline EncodePlan plan_encode(const upr_config& c, int U, const int32_t* hoffs) 
 // Workspace of rank for the candidate rows of `coffs` (host offsets):
 // residual, LayerNorm output, fused q|k|v rows, attention output, FFN hidden
 // (at least head_cols wide: the action heads' hidden layer reuses it), and
-// (bf16 models) the attention work list.  The fp8-projection variant keeps
+// the attention work list.  The fp8-projection variant keeps
 // MXFP8 encodings in the LayerNorm-output and FFN-hidden buffers (codes,
 // then scales at the next 256-byte boundary: rows x cols x 2 bytes hold
 // both for rows x cols >= 256).
 inline RankPlan plan_rank(const upr_config& c, int U, const int32_t* coffs, const int32_t* hoffs,
-                          int head_cols = 0) {
+                          int head_cols = 0, bool lists = true) {
     RankPlan p;
     p.row0 = coffs[0];
     p.rows = (int64_t)coffs[U] - coffs[0];
     if (p.rows <= 0) { p.rows = 0; return p; }
     const size_t es = dtype_bytes(c), R = (size_t)p.rows, d = c.d_model, F = c.d_ff;
-    p.use_mfma_attn = use_mfma_attn(c, true);
-    if (p.use_mfma_attn) {
+    p.use_mfma_attn = use_mfma_attn(c, true, U, hoffs, lists);
+    if (p.use_mfma_attn && !bf16_storage(c)) {
+        p.attn_tile = kF32AttnTile;
+        p.work_items = attn_items(c, U, coffs, p.attn_tile);
+    } else if (p.use_mfma_attn) {
         double seen = 0.0;                  // history rows seen, summed over candidates
         for (int u = 0; u < U; ++u)
             seen += (double)((int64_t)coffs[u + 1] - coffs[u]) * (double)((int64_t)hoffs[u + 1] - hoffs[u]);
@@ -196,6 +210,12 @@ hipError_t launch_attn_rank_mx(const bf16* qkv, uint8_t* codes, uint8_t* scales,
                                int H, int D, const int32_t* work,
                                int64_t items, int tile, const bf16* cache_k, const bf16* cache_v,
                                int64_t cache_cap, hipStream_t s);
+
+// MFMA attention of fp32 models, ranking (q: q|k|v rows) or causal encode (q:
+// query rows), fp32 output; the work list has kF32AttnTile-row items.
+hipError_t launch_attn_f32(bool causal, const float* q, float* o, int64_t row0, int H, int D, const int32_t* work,
+                           int64_t items, const float* cache_k, const float* cache_v, int64_t cache_cap,
+                           hipStream_t s);
 
 // MFMA causal encode attention (bf16 query rows and cache, head_dim 64 or 32),
 // fp16 output.

@@ -335,6 +335,15 @@ void mx_quantize_host(const float* x, int64_t rows, int k, uint8_t* codes, uint8
         }
 }
 
+// The attention work list of a planned call: tiles of the rows of `rows`.
+template <typename Plan>
+static WorkList work_list(const upr_segments* rows, const upr_segments* hist, int H, const Plan& p, bool reverse,
+                          char* ws, int64_t cap) {
+    return WorkList{rows->offsets_dev, hist->offsets_dev, rows->num_users, H, p.attn_tile, reverse ? 1 : 0,
+                    reinterpret_cast<int32_t*>(ws + p.off_work), p.work_items, rows->offsets_host[0],
+                    rows->offsets_host[rows->num_users], cap};
+}
+
 // Candidate layers of the fp8-projection variant: the bf16 sequence with
 // MXFP8 projection operands (LayerNorms write MXFP8 directly, the attention
 // kernel encodes its fp32 output, the FFN-up GEMM writes its GELU output as
@@ -360,10 +369,7 @@ static upr_status rank_layers_mx(const upr_model* m, const upr_kv_cache* cache,
                                               m->layers[0].ln1_g, m->layers[0].ln1_b, c.ln_eps, s));
     if (p.use_mfma_attn)
         UPR_LAUNCH("rank.worklist",
-                   launch_attn_worklist(cand->offsets_dev, hist->offsets_dev, cand->num_users, H,
-                                        p.attn_tile, false, reinterpret_cast<int32_t*>(ws + p.off_work),
-                                        p.work_items, cand->offsets_host[0],
-                                        cand->offsets_host[cand->num_users], cache->capacity_rows, s));
+                   launch_attn_worklist(work_list(cand, hist, H, p, false, ws, cache->capacity_rows), s));
     // LN2 is folded into the O projection (EPI_RESID_LN_MX) when a row fits
     // its tile; it then writes LN2 over its own operand (the attention
     // output): each tile owns whole rows and overwrites them after its last
@@ -592,15 +598,13 @@ static upr_status run_encode(const upr_model* m, const typename Types::kv* hist_
     const float qscale = 1.4426950408889634f / std::sqrt((float)D);
     // bf16 models: the first O projection reads the residual from the tokens
     const bool tok_resid = std::is_same_v<Types, Bf16Types>;
+    const bool list = p.use_mfma_attn && c.n_layers > 1, list_with_ln = list && hist->num_users <= kListMaxUsers;
+    const WorkList wl = work_list(hist, hist, H, p, true, ws, cache->capacity_rows);
     UPR_LAUNCH("encode.init_ln1",
                launch_init_layernorm<T, TA>(hist_emb + p.row0 * d, tok_resid ? nullptr : g, a, R, d,
-                                            m->layers[0].ln1_g, m->layers[0].ln1_b, c.ln_eps, s));
-    if (p.use_mfma_attn && c.n_layers > 1)
-        UPR_LAUNCH("encode.worklist",
-                   launch_attn_worklist(hist->offsets_dev, hist->offsets_dev, hist->num_users, H,
-                                        p.attn_tile, true, reinterpret_cast<int32_t*>(ws + p.off_work),
-                                        p.work_items, hist->offsets_host[0],
-                                        hist->offsets_host[hist->num_users], cache->capacity_rows, s));
+                                            m->layers[0].ln1_g, m->layers[0].ln1_b, c.ln_eps,
+                                            list_with_ln ? &wl : nullptr, s));
+    if (list && !list_with_ln) UPR_LAUNCH("encode.worklist", launch_attn_worklist(wl, s));
     for (int l = 0; l < c.n_layers; ++l) {
         const LayerWeights& w = m->layers[l];
         if (l > 0 && !fused_layernorm<Types>(c))
@@ -694,14 +698,13 @@ static upr_status run_rank(const upr_model* m, const upr_kv_cache* cache,
     if (!mx_done) {
     // bf16 models: the first O projection reads the residual from the tokens
     const bool tok_resid = std::is_same_v<Types, Bf16Types>;
+    const bool list_with_ln = p.use_mfma_attn && cand->num_users <= kListMaxUsers;
+    const WorkList wl = work_list(cand, hist, H, p, false, ws, cache->capacity_rows);
     UPR_LAUNCH("rank.init_ln1",
                launch_init_layernorm<T, TA>(cand_emb + p.row0 * d, tok_resid ? nullptr : g, a, R, d,
-                                            m->layers[0].ln1_g, m->layers[0].ln1_b, c.ln_eps, s));
-    if (p.use_mfma_attn)
-        UPR_LAUNCH("rank.worklist", launch_attn_worklist(cand->offsets_dev, hist->offsets_dev, cand->num_users, H,
-                                     p.attn_tile, false, reinterpret_cast<int32_t*>(ws + p.off_work),
-                                     p.work_items, cand->offsets_host[0],
-                                     cand->offsets_host[cand->num_users], cache->capacity_rows, s));
+                                            m->layers[0].ln1_g, m->layers[0].ln1_b, c.ln_eps,
+                                            list_with_ln ? &wl : nullptr, s));
+    if (p.use_mfma_attn && !list_with_ln) UPR_LAUNCH("rank.worklist", launch_attn_worklist(wl, s));
     for (int l = 0; l < c.n_layers; ++l) {
         const LayerWeights& w = m->layers[l];
         if (l > 0 && !fused_layernorm<Types>(c))

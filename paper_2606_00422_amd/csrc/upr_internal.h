@@ -159,14 +159,36 @@ struct Epilogue {
     float* score_out;       // [M]
 };
 
+// Work list of the matrix-core attention kernels: entries (first history row
+// of the user, history length, first query row, head | query count << 16)
+// over the rows of row_offsets (candidates, or the history itself for
+// encode), users with the longest history first; `reverse` lists each user's
+// tiles last-first (encode: the costliest causal tiles first).  row_first /
+// row_last: the host values of row_offsets[0] and [U]; cap: the cache rows.
+// Device offsets that disagree with them yield empty items.
+struct WorkList {
+    const int32_t* row_offsets;
+    const int32_t* hist_offsets;
+    int U, H, tile, reverse;
+    int32_t* work;
+    int64_t items;          // 0: no list
+    int64_t row_first, row_last, cap;
+};
+// Most users for which the first LayerNorm's launch builds the list with one
+// of its 256-thread blocks (kept out of the LayerNorm's way: the sort is
+// quadratic in the users, 16 us of a 1024-thread block at 2048).
+constexpr int kListMaxUsers = 256;
+
 // ---------------------------------------------------------------------------
 // Launchers (all enqueue on `stream`; they return hipGetLastError()).
 // Row-wise kernels.
 // ---------------------------------------------------------------------------
-// g = float(x) and a = LN(g) in one pass (first layer's LayerNorm).
+// g = float(x) and a = LN(g) in one pass (first layer's LayerNorm); with
+// `wl` one more block, the first, builds the work list (wl->U <= kListMaxUsers).
 template <typename TKV, typename TA>
 hipError_t launch_init_layernorm(const TKV* x, float* g, TA* a, int64_t rows, int d,
-                                 const float* gain, const float* shift, float eps, hipStream_t s);
+                                 const float* gain, const float* shift, float eps, const WorkList* wl,
+                                 hipStream_t s);
 template <typename TA>
 hipError_t launch_layernorm(const float* g, TA* a, int64_t rows, int d, const float* gain,
                             const float* shift, float eps, hipStream_t s);

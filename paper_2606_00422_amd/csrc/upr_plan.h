@@ -186,16 +186,8 @@ hipError_t launch_ffn_fused(const f16* O, const f16* WoP, const Epilogue& epa, c
                             const f16* W2p, const float* b1, float s1, int64_t M, int d, int F,
                             const Epilogue& epi, hipStream_t s);
 
-// Work list of the MFMA attention: entries (first history row of the user,
-// history length, first query row, head | query count << 16) over the rows
-// of `row_offsets` (candidates, or the history itself for encode), users
-// with the longest history first; `reverse` lists
-// each user's tiles last-first (encode: the costliest causal tiles first).
-// row_first / row_last: the host values of row_offsets[0] and [U]; cap: the
-// cache rows.  Device offsets that disagree with them yield empty items.
-hipError_t launch_attn_worklist(const int32_t* row_offsets, const int32_t* hist_offsets, int U,
-                                int H, int tile, bool reverse, int32_t* work, int64_t items,
-                                int64_t row_first, int64_t row_last, int64_t cap, hipStream_t s);
+// Builds the list of `wl` (upr_internal.h) in a launch of its own.
+hipError_t launch_attn_worklist(const WorkList& wl, hipStream_t s);
 
 // MFMA ranking attention (bf16 q|k|v rows and cache, head_dim 64 or 32), fp16 output.
 hipError_t launch_attn_rank(const bf16* qkv, f16* o, int64_t row0, int H, int D,

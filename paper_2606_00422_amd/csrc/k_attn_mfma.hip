@@ -44,6 +44,7 @@
 #include "worklist.h"
 
 #include <cstdlib>
+#include <type_traits>
 
 namespace upr {
 
@@ -63,12 +64,13 @@ constexpr int stage_keys(int D) { return 4096 / D; }
 // others), or 1 for calls too small to fill the device with 128-candidate
 // items (each query's arithmetic is the same either way); the causal pass
 // 2 as well (four waves per SIMD; 64 queries per wave, at two waves per
-// SIMD, read half the K/V per query but measured 26% slower)
-constexpr int kRankQG = 2, kSmallRankQG = 1, kEncodeQG = 2;
+// SIMD, read half the K/V per query but measured 26% slower), 1 in small calls
+constexpr int kRankQG = 2, kSmallRankQG = 1, kEncodeQG = 2, kSmallEncodeQG = 1;
 static_assert(4 * 16 * kRankQG == kRankAttnTile, "ranking work-list tile must match the kernel");
 static_assert(8 * 16 * kRankQG == kLongRankAttnTile, "long-history tile: eight waves of 32 queries");
 static_assert(4 * 16 * kSmallRankQG == kSmallRankAttnTile, "small-call tile must match the kernel");
 static_assert(4 * 16 * kEncodeQG == kAttnTile, "encode work-list tile must match the kernel");
+static_assert(4 * 16 * kSmallEncodeQG == kSmallAttnTile, "small encode tile must match the kernel");
 
 // LDS layout of a stage: rows (keys) of 2D bytes, their 16-byte chunks
 // XOR-swizzled.  K fragment reads take 16 consecutive rows at one chunk; a
@@ -261,20 +263,58 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
     }
 
     // One 32-key sub-block (keys kb .. kb+31 of the stage in cK / cV).
-    auto sub_block = [&](const bf16* cK, const bf16* cV, int kb, int kabs) __attribute__((always_inline)) {
-        if (!wave_active || (CAUSAL && kabs > wave_last)) return;   // nothing to do for this wave
-        // S^T - m for 32 keys x 64 queries
-        f32x4 s[kQG][2];
-        // The MFMA runs of a wave take issue priority over the other wave on
-        // its SIMD, whose exponentials then fill the matrix core's gaps.
-        __builtin_amdgcn_s_setprio(1);
+    typedef b8 KFrag[2][kES];               // [16-key half][32-value step]
+    auto read_k = [&](const bf16* cK, int kb, KFrag& kf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int row = kb + t * 16 + l16;
+#pragma unroll
+            for (int es = 0; es < kES; ++es)
+                kf[t][es] = *reinterpret_cast<const b8*>(&cK[row * kD + (((es * 4 + g) ^ key_k<kD>(row)) << 3)]);
+        }
+    };
+    // V^T fragment of e-block eb: lane (g, i) needs V[key(8g + j)][16eb + i];
+    // in each 16-lane group, lane s of a transposing read addresses row
+    // 4g + s/4 (+16), dims 16eb + 4(s%4).
+    auto read_v = [&](const bf16* cV, int kb, int eb) __attribute__((always_inline)) {
+        b8 vf;
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) {
+            const int row = kb + 16 * hh + 4 * g + (l16 >> 2);
+            const int ch = 2 * eb + ((l16 & 3) >> 1);
+            const bf16* p = &cV[row * kD + ((ch ^ key_v<kD>(row)) << 3) + ((l16 & 1) << 2)];
+            const b4v v4 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
+                (__attribute__((address_space(3))) b4v*)(p));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) vf[4 * hh + j] = v4[j];
+        }
+        return vf;
+    };
+    // The MFMA runs of a wave take issue priority over the other waves on its
+    // SIMD, whose exponentials then fill the matrix core's gaps.  Small items
+    // (kQG = 1) run alone on their SIMD: their K and V fragments are read
+    // ahead of the arithmetic instead (READ_AHEAD).
+    constexpr bool kReadAhead = kQG == 1;
+    auto prio = [](auto p) __attribute__((always_inline)) {
+        if constexpr (!kReadAhead) __builtin_amdgcn_s_setprio(decltype(p)::value);
+    };
+    typedef std::integral_constant<int, 1> high;
+    typedef std::integral_constant<int, 0> low;
+    // logits of a sub-block: S^T - m for 32 keys, masked
+    auto logits = [&](const bf16* cK, int kb, int kabs, f32x4 (&s)[kQG][2], const KFrag* ahead)
+        __attribute__((always_inline)) {
+        prio(high{});
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             b8 kf[kES];
             const int row = kb + t * 16 + l16;
 #pragma unroll
-            for (int es = 0; es < kES; ++es)
-                kf[es] = *reinterpret_cast<const b8*>(&cK[row * kD + (((es * 4 + g) ^ key_k<kD>(row)) << 3)]);
+            for (int es = 0; es < kES; ++es) {
+                if constexpr (kReadAhead)
+                    kf[es] = (*ahead)[t][es];
+                else
+                    kf[es] = *reinterpret_cast<const b8*>(&cK[row * kD + (((es * 4 + g) ^ key_k<kD>(row)) << 3)]);
+            }
 #pragma unroll
             for (int qg = 0; qg < kQG; ++qg) {
                 s[qg][t] = negm[qg];
@@ -283,7 +323,7 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
                     s[qg][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[es], qf[qg][es], s[qg][t], 0, 0, 0);
             }
         }
-        __builtin_amdgcn_s_setprio(0);
+        prio(low{});
         // ranking: mask keys past the history end (last sub-block only);
         // encode: mask keys after the query (diagonal sub-blocks only)
         if (__builtin_expect(CAUSAL ? kabs + 31 > wave_first : kabs + 32 > n, 0)) {
@@ -297,6 +337,9 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
                         if (CAUSAL ? key > qpos[qg] : key >= n) s[qg][t][r] = -INFINITY;
                 }
         }
+    };
+    // probabilities, row sums and O^T += V^T P^T of a sub-block
+    auto weigh = [&](const bf16* cV, int kb, const f32x4 (&s)[kQG][2], const b8* ahead) __attribute__((always_inline)) {
         b8 pf[kQG], pl[kQG];                // probabilities (kSplitP: hi and lo)
 #pragma unroll
         for (int qg = 0; qg < kQG; ++qg) {
@@ -319,23 +362,14 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
                 }
             }
         }
-        // O^T += V^T P^T.  V^T fragment of e-block eb: lane (g, i) needs
-        // V[key(8g + j)][16eb + i]; in each 16-lane group, lane s of a
-        // transposing read addresses row 4g + s/4 (+16), dims 16eb + 4(s%4).
-        __builtin_amdgcn_s_setprio(1);
+        prio(high{});
 #pragma unroll
         for (int eb = 0; eb < kEB; ++eb) {
             b8 vf;
-#pragma unroll
-            for (int hh = 0; hh < 2; ++hh) {
-                const int row = kb + 16 * hh + 4 * g + (l16 >> 2);
-                const int ch = 2 * eb + ((l16 & 3) >> 1);
-                const bf16* p = &cV[row * kD + ((ch ^ key_v<kD>(row)) << 3) + ((l16 & 1) << 2)];
-                const b4v v4 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-                    (__attribute__((address_space(3))) b4v*)(p));
-#pragma unroll
-                for (int j = 0; j < 4; ++j) vf[4 * hh + j] = v4[j];
-            }
+            if constexpr (kReadAhead)
+                vf = ahead[eb];
+            else
+                vf = read_v(cV, kb, eb);
 #pragma unroll
             for (int qg = 0; qg < kQG; ++qg) {
                 o[qg][eb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[qg], o[qg][eb], 0, 0, 0);
@@ -343,16 +377,44 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
                     o[qg][eb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pl[qg], o[qg][eb], 0, 0, 0);
             }
         }
-        __builtin_amdgcn_s_setprio(0);
+        prio(low{});
+    };
+    auto sub_block = [&](const bf16* cK, const bf16* cV, int kb, int kabs) __attribute__((always_inline)) {
+        if (!wave_active || (CAUSAL && kabs > wave_last)) return;   // nothing to do for this wave
+        f32x4 s[kQG][2];
+        logits(cK, kb, kabs, s, nullptr);
+        weigh(cV, kb, s, nullptr);
     };
 
     auto stage = [&](const bf16* cK, const bf16* cV, bf16* nK, bf16* nV, int st) __attribute__((always_inline)) {
         if (st + 1 < nst) issue_loads(nK, nV, st + 1);
         const int k0 = st * kKS;
-        sub_block(cK, cV, 0, k0);
+        if constexpr (kReadAhead) {
+            // sub-block i's V fragments and sub-block i + 1's K fragments
+            // (rows of the stage whether or not they hold keys) are read
+            // before its arithmetic
+            if (wave_active && !(CAUSAL && k0 > wave_last)) {
+                KFrag kf[2];
+                read_k(cK, 0, kf[0]);
 #pragma unroll
-        for (int kb = 32; kb < kKS; kb += 32)
-            if (k0 + kb < nkeys) sub_block(cK, cV, kb, k0 + kb);
+                for (int i = 0; i < kKS / 32; ++i) {
+                    const int kabs = k0 + 32 * i;
+                    if (i > 0 && (kabs >= nkeys || (CAUSAL && kabs > wave_last))) break;
+                    b8 vf[kEB];
+#pragma unroll
+                    for (int eb = 0; eb < kEB; ++eb) vf[eb] = read_v(cV, 32 * i, eb);
+                    if (i + 1 < kKS / 32) read_k(cK, 32 * i + 32, kf[(i + 1) & 1]);
+                    f32x4 s[kQG][2];
+                    logits(cK, 32 * i, kabs, s, &kf[i & 1]);
+                    weigh(cV, 32 * i, s, vf);
+                }
+            }
+        } else {
+            sub_block(cK, cV, 0, k0);
+#pragma unroll
+            for (int kb = 32; kb < kKS; kb += 32)
+                if (k0 + kb < nkeys) sub_block(cK, cV, kb, k0 + kb);
+        }
         __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0): next stage landed
         __syncthreads();
     };
@@ -543,14 +605,23 @@ hipError_t launch_attn_encode(const bf16* q, f16* o, int64_t row0, int H, int D,
                               int tile, const bf16* cache_k, const bf16* cache_v,
                               int64_t cache_cap, hipStream_t s) {
     if (items == 0) return hipSuccess;
-    if ((D != 64 && D != 32) || tile != kAttnTile) return hipErrorInvalidValue;
+    if ((D != 64 && D != 32) || (tile != kAttnTile && tile != kSmallAttnTile)) return hipErrorInvalidValue;
     const int4* w = reinterpret_cast<const int4*>(work);
-    if (D == 64)
-        k_attn_mfma<true, kEncodeQG><<<(unsigned)items, 256, 0, s>>>(
-            q, (int64_t)H * D, o, nullptr, row0, H, w, cache_k, cache_v, cache_cap, force_exact_flag());
+    const int64_t ld = (int64_t)H * D;
+    const int exact = force_exact_flag();
+    const unsigned grid = (unsigned)items;
+    if (D == 64 && tile == kAttnTile)
+        k_attn_mfma<true, kEncodeQG><<<grid, 256, 0, s>>>(q, ld, o, nullptr, row0, H, w, cache_k, cache_v,
+                                                         cache_cap, exact);
+    else if (D == 64)
+        k_attn_mfma<true, kSmallEncodeQG><<<grid, 256, 0, s>>>(q, ld, o, nullptr, row0, H, w, cache_k, cache_v,
+                                                              cache_cap, exact);
+    else if (tile == kAttnTile)
+        k_attn_mfma<true, kEncodeQG, false, 4, 32><<<grid, 256, 0, s>>>(q, ld, o, nullptr, row0, H, w, cache_k,
+                                                                       cache_v, cache_cap, exact);
     else
-        k_attn_mfma<true, kEncodeQG, false, 4, 32><<<(unsigned)items, 256, 0, s>>>(
-            q, (int64_t)H * D, o, nullptr, row0, H, w, cache_k, cache_v, cache_cap, force_exact_flag());
+        k_attn_mfma<true, kSmallEncodeQG, false, 4, 32><<<grid, 256, 0, s>>>(q, ld, o, nullptr, row0, H, w, cache_k,
+                                                                            cache_v, cache_cap, exact);
     return hipGetLastError();
 }
 

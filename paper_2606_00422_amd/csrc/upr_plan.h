@@ -15,6 +15,10 @@ inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 // many history rows, in the causal encode pass, or candidates, in ranking,
 // of one user for one head).
 constexpr int kAttnTile = 128;
+// (encode calls with few work items: a wave's walk over the keys is as long
+// with 64-row items but carries half the queries)
+constexpr int kSmallAttnTile = 64;
+constexpr int64_t kSmallItems = 512;        // fewer 128-row items than this
 constexpr int kRankAttnTile = 128;
 constexpr int kSmallRankAttnTile = 64;      // ranking calls with few work items
 constexpr int64_t kSmallRankItems = 512;    // fewer 128-candidate items than this
@@ -63,7 +67,8 @@ inline int64_t attn_items(const upr_config& c, int U, const int32_t* offs, int t
 //  * for the fp8 variant's ranking pass (head_dim 32: the matrix-core kernel's
 //    MXFP8 output covers whole 64-value heads), and
 //  * where the list does not fit (`lists` false): a workspace that held these
-//    calls before they had a list still does.
+//    calls before they had a list still does.  (bf16 encode at head_dim 64
+//    then takes its larger items, whose list is half as long.)
 inline bool use_mfma_attn(const upr_config& c, bool rank, int U, const int32_t* hoffs, bool lists) {
     if (bf16_storage(c) && c.head_dim == 64) return true;
     if (!lists || (rank && c.dtype == UPR_BF16_MXFP8)) return false;
@@ -83,7 +88,10 @@ inline EncodePlan plan_encode(const upr_config& c, int U, const int32_t* hoffs, 
     if (p.rows <= 0) { p.rows = 0; return p; }
     const size_t es = dtype_bytes(c), R = (size_t)p.rows, d = c.d_model, F = c.d_ff;
     p.use_mfma_attn = use_mfma_attn(c, false, U, hoffs, lists);
-    if (!bf16_storage(c)) p.attn_tile = kF32AttnTile;
+    if (!bf16_storage(c))
+        p.attn_tile = kF32AttnTile;
+    else if (lists && attn_items(c, U, hoffs, kAttnTile) < kSmallItems)
+        p.attn_tile = kSmallAttnTile;
     if (p.use_mfma_attn) p.work_items = attn_items(c, U, hoffs, p.attn_tile);
     size_t o = 0;
     p.off_g = o; o = align256(o + R * d * 4);

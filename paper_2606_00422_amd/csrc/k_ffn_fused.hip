@@ -8,11 +8,11 @@
 // residual+LN2 epilogue, FFN up with a GELU epilogue, FFN down) writes and
 // re-reads R x d + R x F fp16 values through HBM per layer.
 //
-// One workgroup = 128 rows (TM = 4 row tiles of 32) and the whole output
-// row; eight waves.  Calls whose 128-row tiles would leave compute units idle
-// run the unfused sequence on short tiles instead (ffn_fused_rows), with the
-// same results bit for bit: both feed the matrix cores the same products in
-// the same order and round the same sums in the same order.
+// One workgroup = 128 rows (TM = 4 row tiles of 32), or 64 (TM = 2) in calls
+// of medium size, and the whole output row; eight waves.  Smaller calls run
+// the unfused sequence on small tiles instead (ffn_fused_tile), with the same
+// results bit for bit: all feed the matrix cores the same products in the
+// same order and round the same sums in the same order.
 //  * The tile's rows of the attention output o are loaded into LDS (d/64
 //    blocks of [rows x 64], the GEMM's swizzled 128-byte rows).
 //  * O projection: the eight waves side by side along the output (64
@@ -27,7 +27,7 @@
 //    residual never goes to HBM: it stays in the accumulators, divided by
 //    W2's power-of-two scale, as the FFN down's starting value.
 //  * The hidden dimension is walked in chunks of 128.  Up phase: waves in a
-//    2 (rows) x 4 (hidden columns) grid compute h = a W1c^T, 64 x 32 each.
+//    2 (rows) x 4 (hidden columns) grid compute h = a W1c^T, 16 TM x 32 each.
 //    Bias and GELU are applied in registers and the fp16 values go to the
 //    chunk buffer in LDS.  Down phase: as the O projection, the eight waves
 //    accumulate h W2c^T into the fp32 tile that the final epilogue consumes.
@@ -268,7 +268,8 @@ __global__ __launch_bounds__(512, 1) void k_ffn_fused(const f16* __restrict__ O,
     constexpr int kD = 64 * KB;
     constexpr int kUpSteps = 4 * KB;                   // 16-deep k-steps of the up phase
     constexpr int kSteps = kUpSteps + 2 * kDownSteps;  // weight fragments per chunk (and per block)
-    constexpr int kUT = TM >= 2 ? TM / 2 : 1;          // up-phase row tiles per wave
+    constexpr int kUT = TM / 2;                        // up-phase row tiles per wave
+    static_assert(TM == 2 || TM == 4, "two wave rows of whole tiles");
     constexpr int kRing = ring_depth<KB>();
     static_assert(kSteps % kRing == 0 && kRing <= kUpSteps, "ring slots repeat every block");
     __shared__ __attribute__((aligned(16))) char smem[smem_bytes<TM>()];
@@ -290,10 +291,9 @@ __global__ __launch_bounds__(512, 1) void k_ffn_fused(const f16* __restrict__ O,
     const int nch = F / kFC;
     const int fsteps = F / 16;
 
-    // up-phase role: rows 64 um .. (TM = 1: 32 rows on waves 0-3), hidden
-    // columns 32 un ..
-    const int um = TM >= 2 ? wave >> 2 : 0, un = wave & 3;
-    const bool up_on = TM >= 2 || wave < 4;
+    // up-phase role: row tiles kUT um .., hidden columns 32 un ..
+    const int um = wave >> 2, un = wave & 3;
+    constexpr bool up_on = true;
     // down-phase role: output columns 64 wave .. +63
     const bool dn_on = kD == kMaxD || wave * 64 < kD;
 
@@ -393,7 +393,7 @@ __global__ __launch_bounds__(512, 1) void k_ffn_fused(const f16* __restrict__ O,
         const char* base = reinterpret_cast<const char*>(sA + (s >> 2) * kRows * 64);
 #pragma unroll
         for (int i = 0; i < kUT; ++i)
-            dst[i] = *reinterpret_cast<const h8*>(base + (um * 64 + i * 32 + lrow) * 128 + choff[s & 3]);
+            dst[i] = *reinterpret_cast<const h8*>(base + ((um * kUT + i) * 32 + lrow) * 128 + choff[s & 3]);
     };
     // hidden fragment q = kk' TM + i (k-step kk', row tile i)
     auto h_frag = [&](int q) __attribute__((always_inline)) -> h8 {
@@ -558,7 +558,7 @@ __global__ __launch_bounds__(512, 1) void k_ffn_fused(const f16* __restrict__ O,
                 for (int b = 0; b < 2; ++b) {
                     const int kkp = 2 * un + b;                 // down-phase k-step
                     char* dst = reinterpret_cast<char*>(sH + (kkp >> 2) * kRows * 64) +
-                                (um * 64 + i * 32 + lrow) * 128 + choff[kkp & 3];
+                                ((um * kUT + i) * 32 + lrow) * 128 + choff[kkp & 3];
                     *reinterpret_cast<u32x4*>(dst) = u32x4{pk[i][b][0], pk[i][b][1], pk[i][b][2], pk[i][b][3]};
                 }
         }
@@ -651,25 +651,40 @@ hipError_t launch_kb(int KB, unsigned grid, const f16* O, const h8* WoP, const h
 }
 
 template <int MODE>
-hipError_t launch_mode(const f16* O, const h8* WoP, const Epilogue& epa, const h8* W1p, const h8* W2p,
+hipError_t launch_mode(int tile, const f16* O, const h8* WoP, const Epilogue& epa, const h8* W1p, const h8* W2p,
                        const float* b1, float s1, int64_t M, int d, int F, const Epilogue& epi, hipStream_t s) {
-    return launch_kb<MODE, 4>(d / 64, (unsigned)((M + 127) / 128), O, WoP, W1p, W2p, b1, s1, M, F, epa, epi, s);
+    const unsigned grid = (unsigned)((M + tile - 1) / tile);
+    return tile == 128 ? launch_kb<MODE, 4>(d / 64, grid, O, WoP, W1p, W2p, b1, s1, M, F, epa, epi, s)
+                       : launch_kb<MODE, 2>(d / 64, grid, O, WoP, W1p, W2p, b1, s1, M, F, epa, epi, s);
 }
 
 }  // namespace ffn_detail
 
-bool ffn_fused_rows(int64_t M) { return (M + 127) / 128 >= gemm_detail::device_cus(); }
+// us per layer tail, unfused / 64-row / 128-row tiles (F = 4d):
+//   d 128: 4000 rows 21 / 22 / 36, 8000 30 / 22 / 37, 20000 60 / 42 / 37
+//   d 256: 4000 rows 30 / 36 / 57, 8000 42 / 38 / 58, 16000 63 / 39 / 59, 20000 81 / 74 / 61
+//   d 512: 8000 rows 73 / 84 / 116, 10000 100 / 86 / 119, 16000 128 / 95 / 126, 24000 191 / 172 / 132
+// A tail tile takes about the same time however few of them run, the unfused
+// sequence grows with the rows: 64-row tiles from 16 (d 128) to 32 rows per
+// compute unit (d >= 384), 128-row tiles once 64-row tiles would need a second
+// round.
+int ffn_fused_tile(int64_t M, int d) {
+    const int64_t cus = gemm_detail::device_cus();
+    if (M > 64 * cus) return 128;
+    const int per_cu = 8 + d / 16 < 32 ? 8 + d / 16 : 32;
+    return M > cus * per_cu ? 64 : 0;
+}
 
 bool ffn_fused_supported(int d, int F) {
     return (d == 128 || d == 256 || d == 384 || d == 512) && F > 0 && F % ffn_detail::kFC == 0;
 }
 
-hipError_t launch_ffn_fused(const f16* O, const f16* WoP, const Epilogue& epa, const f16* W1p,
+hipError_t launch_ffn_fused(int tile, const f16* O, const f16* WoP, const Epilogue& epa, const f16* W1p,
                             const f16* W2p, const float* b1, float s1, int64_t M, int d, int F,
                             const Epilogue& epi, hipStream_t s) {
     using namespace ffn_detail;
     if (M == 0) return hipSuccess;
-    if (!ffn_fused_supported(d, F) || epi.ldr != d || !epi.ln_gain || !epi.ln_shift)
+    if ((tile != 64 && tile != 128) || !ffn_fused_supported(d, F) || epi.ldr != d || !epi.ln_gain || !epi.ln_shift)
         return hipErrorInvalidValue;
     if (epa.mode != EPI_RESID_LN || epa.acc_resid || epa.resid != epi.resid || epa.ldr != d || !epa.bias ||
         !epa.ln_gain || !epa.ln_shift || !epi.acc_resid)
@@ -680,10 +695,10 @@ hipError_t launch_ffn_fused(const f16* O, const f16* WoP, const Epilogue& epa, c
     switch (epi.mode) {
         case EPI_RESID_LN:
             if (!epi.ln_out || epi.ln_ldo % 4 != 0) return hipErrorInvalidValue;
-            return launch_mode<EPI_RESID_LN>(O, wo, epa, w1, w2, b1, s1, M, d, F, epi, s);
+            return launch_mode<EPI_RESID_LN>(tile, O, wo, epa, w1, w2, b1, s1, M, d, F, epi, s);
         case EPI_RESID_SCORE:
             if (!epi.score_w || !epi.score_b || !epi.score_out) return hipErrorInvalidValue;
-            return launch_mode<EPI_RESID_SCORE>(O, wo, epa, w1, w2, b1, s1, M, d, F, epi, s);
+            return launch_mode<EPI_RESID_SCORE>(tile, O, wo, epa, w1, w2, b1, s1, M, d, F, epi, s);
         default: return hipErrorInvalidValue;
     }
 }

@@ -487,9 +487,10 @@ static hipError_t launch_ffn_block(const char* const names[7], const upr_config&
     r.resid_src = resid_src;
     // the layer's tail in one kernel (O projection, residual update, LN2,
     // FFN with its hidden rows on chip, then the next LayerNorm or the score
-    // head) for calls whose 128-row tiles fill the device
+    // head) for calls with enough rows for its tiles
+    const int tail_tile = ffn_fused_tile(R, d);
     const bool tail = std::is_same_v<Types, Bf16Types> && fuse && w.WoP != nullptr && w.W1p != nullptr &&
-                      (next_g != nullptr || scores != nullptr) && ffn_fused_rows(R);
+                      (next_g != nullptr || scores != nullptr) && tail_tile != 0;
     const bool sep_o = fuse && !tail && separate_layernorm(R, d, d);
     if (!tail) {
         if (sep_o) r.mode = EPI_RESID;
@@ -528,7 +529,7 @@ static hipError_t launch_ffn_block(const char* const names[7], const upr_config&
                 r.ln_shift = next_b;
             }
             ProfScope ps(names[4], s);
-            return launch_ffn_fused(reinterpret_cast<const f16*>(o), static_cast<const f16*>(w.WoP), oproj,
+            return launch_ffn_fused(tail_tile, reinterpret_cast<const f16*>(o), static_cast<const f16*>(w.WoP), oproj,
                                     static_cast<const f16*>(w.W1p), static_cast<const f16*>(w.W2p), w.b1,
                                     w.s_1, R, d, F, r, s);
         }

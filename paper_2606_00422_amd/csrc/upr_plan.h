@@ -186,11 +186,11 @@ hipError_t launch_gemm_small(const TA* A, int64_t lda, const TA* W, int64_t M, i
 // W1p [F, d] and W2p [d, F] in the fragment-major layout the model image
 // builds; s1 = W1's scale.
 bool ffn_fused_supported(int d, int F);
-// Whether a call of M rows takes the fused kernel: its 128-row tiles must
-// fill the device.  Smaller calls run the unfused sequence on short tiles,
-// with bit-identical results (same products in the same order).
-bool ffn_fused_rows(int64_t M);
-hipError_t launch_ffn_fused(const f16* O, const f16* WoP, const Epilogue& epa, const f16* W1p,
+// Rows of the fused kernel's tiles in a call of M rows: 128, 64, or 0 when
+// the call runs the unfused sequence on small tiles, which is faster for few
+// rows.  The results are the same bits (same products in the same order).
+int ffn_fused_tile(int64_t M, int d);
+hipError_t launch_ffn_fused(int tile, const f16* O, const f16* WoP, const Epilogue& epa, const f16* W1p,
                             const f16* W2p, const float* b1, float s1, int64_t M, int d, int F,
                             const Epilogue& epi, hipStream_t s);
 

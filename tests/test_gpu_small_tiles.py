@@ -1,6 +1,7 @@
 """The tile a projection runs on depends on the size of the call and never
 changes a result: the same candidates ranked in calls of 1 to 33,000 rows
-(32-, 64-, 128- and 256-wide tiles, whole-row tiles, the fused tail; with the
+(32-, 64-, 128- and 256-wide tiles, whole-row tiles, the fused tail on 64 and
+128 rows; with the
 LayerNorms and the score head inside an epilogue or as launches of their own)
 get the same bits, and a sample of them agrees with the oracle."""
 import numpy as np
@@ -18,7 +19,8 @@ pytestmark = pytest.mark.gpu
 CASES = [
     (64, 1, 2, 64, "bf16", 20000),
     (320, 5, 1, 576, "bf16", 20000),        # no fused tail: whole-row tiles
-    (256, 4, 2, 512, "bf16", 33000),        # fused tail in the largest call
+    (128, 2, 1, 384, "bf16", 33000),        # fused tails from 4,097 rows up
+    (256, 4, 2, 512, "bf16", 33000),
     (512, 8, 1, 1024, "bf16", 33000),
     (768, 12, 1, 832, "bf16", 9000),        # rows past the whole-row tile
     (64, 2, 2, 192, "f32", 9000),
@@ -35,7 +37,8 @@ def test_call_size_does_not_change_scores(case):
     run.rank()
     ref = run.scores_np().copy()
     assert np.all(np.isfinite(ref))
-    for lo, hi in ((0, 1), (5, 68), (63, 127), (100, 228), (7, 1000), (1000, 3050), (0, 4097), (11, top // 2)):
+    for lo, hi in ((0, 1), (5, 68), (63, 127), (100, 228), (7, 1000), (1000, 3050), (0, 4097),
+                   (3, 8999), (11, top // 2)):
         say(f"[gpu] small tiles d={d} F={F} {dt}: rows {lo}..{hi} of {top}")
         run.scores.fill_(float("nan"))
         run.rank(coff=np.array([lo, hi], np.int32))

@@ -4,7 +4,7 @@
 //
 // Block tile 256 (rows of A) x 256 (rows of W), K in steps of 64, eight
 // waves in a 2 (M) x 4 (N) grid, each owning 128 x 64 outputs = 4 x 2 MFMA
-// tiles.  The MFMA computes the transposed tile, C^T = W A^T (W as the
+// tiles (and 192, 128 or 64 rows for calls that fill the device better so).  The MFMA computes the transposed tile, C^T = W A^T (W as the
 // first operand), so each lane holds runs of four consecutive output
 // columns of one row.
 //
@@ -381,13 +381,24 @@ __global__ __launch_bounds__(kThreads, 1) void k_gemm_mfma(const void* __restric
         store_tile<MODE, kTM>(acc, region, m0 + wm * kWM, n0 + wn * kWN, M, N, epi, lane,
                               reinterpret_cast<float*>(sA0), wn, reinterpret_cast<float*>(sA1));
     } else {
-        const int wsel = __builtin_amdgcn_readfirstlane(wave) >> 1;
-        f16* const sbase = wsel == 0 ? sA0 : wsel == 1 ? sA1 : wsel == 2 ? sB0 : sB1;
-        const int w3 = __builtin_amdgcn_readfirstlane(wave) / 3;
-        char* const region =
-            kStages == 3 ? reinterpret_cast<char*>(w3 == 0 ? sB0 : w3 == 1 ? sB1 : sB2) +
-                               (__builtin_amdgcn_readfirstlane(wave) % 3) * kShortRegion
-                         : reinterpret_cast<char*>(sbase) + (wave & 1) * kRegionBytes;
+        // staging regions: two in each of the four stage arrays; short tiles
+        // (A stages too small) three in each of the W stages; 128-row tiles
+        // one in each A stage and three in each W stage
+        constexpr int kRegion = kTM == 4 ? kRegionBytes : kShortRegion;
+        char* region;
+        if constexpr (kStages == 3) {
+            const int w3 = wave / 3;
+            region = reinterpret_cast<char*>(w3 == 0 ? sB0 : w3 == 1 ? sB1 : sB2) + (wave % 3) * kRegion;
+        } else if constexpr (kTM == 2) {
+            static_assert(kTM != 2 || SH::kWide || (kRegion <= kBM * kBK * 2 && 3 * kRegion <= kBN * kBK * 2), "regions fit");
+            region = wave < 2 ? reinterpret_cast<char*>(wave == 0 ? sA0 : sA1)
+                              : reinterpret_cast<char*>(wave < 5 ? sB0 : sB1) + ((wave - 2) % 3) * kRegion;
+        } else {
+            static_assert(SH::kWide || kStages == 3 || kTM == 2 || 2 * kRegion <= kBM * kBK * 2, "regions fit");
+            const int wsel = wave >> 1;
+            f16* const sbase = wsel == 0 ? sA0 : wsel == 1 ? sA1 : wsel == 2 ? sB0 : sB1;
+            region = reinterpret_cast<char*>(sbase) + (wave & 1) * kRegion;
+        }
         // Epilogues writing new outputs start only after the trailing
         // waves' last MFMAs (overlapping them measured 4-5% slower); the
         // residual update, which reads as much as it writes, overlaps them.
@@ -404,15 +415,26 @@ int64_t tile_count(int64_t M, int N) {
     return ((M + SH::kBM - 1) / SH::kBM) * (int64_t)((N + SH::kBN - 1) / SH::kBN);
 }
 
+// tm: height of the tiles in 32 rows per wave (1 to 4), 0: the tallest that
+// fill the device, else the shortest.
 template <int MODE, bool MX>
-hipError_t launch_mode(const void* A, int64_t lda, const void* W, const uint8_t* As,
+hipError_t launch_mode(int tm, const void* A, int64_t lda, const void* W, const uint8_t* As,
                        const uint8_t* Ws, int64_t M, int N, int K, const Epilogue& epi,
                        hipStream_t s) {
     // The MXFP8 residual update with LayerNorm takes 64-row tiles: two
     // 128 x 512 stages fill the LDS and leave no room for their scales.
     constexpr int kTall = (MX && Shape<MODE, 4>::kWide) ? 2 : 4;
     const int64_t tall = tile_count<MODE, kTall>(M, N);
-    if (tall >= device_cus()) {
+    if constexpr (!MX && !Shape<MODE, 4>::kWide) {
+        if (tm == 2 || tm == 3) {
+            if (tm == 2)
+                k_gemm_mfma<MODE, MX, 2><<<(unsigned)tile_count<MODE, 2>(M, N), kThreads, 0, s>>>(A, lda, W, As, Ws, M, N, K, epi);
+            else
+                k_gemm_mfma<MODE, MX, 3><<<(unsigned)tile_count<MODE, 3>(M, N), kThreads, 0, s>>>(A, lda, W, As, Ws, M, N, K, epi);
+            return hipGetLastError();
+        }
+    }
+    if (tm == 0 ? tall >= device_cus() : tm == 4) {
         k_gemm_mfma<MODE, MX, kTall><<<(unsigned)tall, kThreads, 0, s>>>(A, lda, W, As, Ws, M, N, K, epi);
     } else {
         const int64_t shorts = tile_count<MODE, 1>(M, N);
@@ -423,7 +445,7 @@ hipError_t launch_mode(const void* A, int64_t lda, const void* W, const uint8_t*
 
 }  // namespace gemm_detail
 
-hipError_t launch_gemm_mfma(const f16* A, int64_t lda, const f16* W, int64_t M, int N, int K,
+hipError_t launch_gemm_mfma(int tm, const f16* A, int64_t lda, const f16* W, int64_t M, int N, int K,
                             const Epilogue& epi, hipStream_t s) {
     using namespace gemm_detail;
     if (M == 0) return hipSuccess;
@@ -432,31 +454,31 @@ hipError_t launch_gemm_mfma(const f16* A, int64_t lda, const f16* W, int64_t M, 
     switch (epi.mode) {
         case EPI_STORE:
             if (epi.ldo % 8 != 0 || epi.scale_cols % 4 != 0) return hipErrorInvalidValue;
-            return launch_mode<EPI_STORE, false>(A, lda, W, nullptr, nullptr, M, N, K, epi, s);
+            return launch_mode<EPI_STORE, false>(tm, A, lda, W, nullptr, nullptr, M, N, K, epi, s);
         case EPI_GELU:
             if (epi.ldo % 8 != 0) return hipErrorInvalidValue;
-            return launch_mode<EPI_GELU, false>(A, lda, W, nullptr, nullptr, M, N, K, epi, s);
+            return launch_mode<EPI_GELU, false>(tm, A, lda, W, nullptr, nullptr, M, N, K, epi, s);
         case EPI_GELU_PERM:
             if (epi.ldo % 16 != 0 || N % 16 != 0) return hipErrorInvalidValue;
-            return launch_mode<EPI_GELU_PERM, false>(A, lda, W, nullptr, nullptr, M, N, K, epi, s);
+            return launch_mode<EPI_GELU_PERM, false>(tm, A, lda, W, nullptr, nullptr, M, N, K, epi, s);
         case EPI_RESID:
             if (epi.ldr % 4 != 0) return hipErrorInvalidValue;
-            return launch_mode<EPI_RESID, false>(A, lda, W, nullptr, nullptr, M, N, K, epi, s);
+            return launch_mode<EPI_RESID, false>(tm, A, lda, W, nullptr, nullptr, M, N, K, epi, s);
         case EPI_RESID_LN:
             static_assert(Shape<EPI_RESID_LN, 4>::kBN == kResidLnMaxN, "tile spans the widest row");
             if (epi.ldr % 4 != 0 || N > kResidLnMaxN || epi.ln_ldo % 4 != 0 ||
                 !epi.ln_gain || !epi.ln_shift || !epi.ln_out)
                 return hipErrorInvalidValue;
-            return launch_mode<EPI_RESID_LN, false>(A, lda, W, nullptr, nullptr, M, N, K, epi, s);
+            return launch_mode<EPI_RESID_LN, false>(tm, A, lda, W, nullptr, nullptr, M, N, K, epi, s);
         case EPI_RESID_SCORE:
             if (epi.ldr % 4 != 0 || N > kResidLnMaxN || !epi.ln_gain || !epi.ln_shift ||
                 !epi.score_w || !epi.score_b || !epi.score_out)
                 return hipErrorInvalidValue;
-            return launch_mode<EPI_RESID_SCORE, false>(A, lda, W, nullptr, nullptr, M, N, K, epi, s);
+            return launch_mode<EPI_RESID_SCORE, false>(tm, A, lda, W, nullptr, nullptr, M, N, K, epi, s);
         case EPI_QKV_CACHE:
             if (epi.ldo % 8 != 0 || epi.head_dim % 8 != 0 || epi.d_model % 8 != 0)
                 return hipErrorInvalidValue;
-            return launch_mode<EPI_QKV_CACHE, false>(A, lda, W, nullptr, nullptr, M, N, K, epi, s);
+            return launch_mode<EPI_QKV_CACHE, false>(tm, A, lda, W, nullptr, nullptr, M, N, K, epi, s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -471,19 +493,19 @@ hipError_t launch_gemm_mx(const uint8_t* A, const uint8_t* A_scales, const uint8
     switch (epi.mode) {
         case EPI_STORE:
             if (epi.ldo % 8 != 0 || epi.scale_cols % 4 != 0) return hipErrorInvalidValue;
-            return launch_mode<EPI_STORE, true>(A, K, W, A_scales, W_scales, M, N, K, epi, s);
+            return launch_mode<EPI_STORE, true>(0, A, K, W, A_scales, W_scales, M, N, K, epi, s);
         case EPI_RESID:
             if (epi.ldr % 4 != 0) return hipErrorInvalidValue;
-            return launch_mode<EPI_RESID, true>(A, K, W, A_scales, W_scales, M, N, K, epi, s);
+            return launch_mode<EPI_RESID, true>(0, A, K, W, A_scales, W_scales, M, N, K, epi, s);
         case EPI_GELU_MX:
             if (N % 64 != 0 || epi.ldo % 64 != 0 || !epi.out_scales) return hipErrorInvalidValue;
-            return launch_mode<EPI_GELU_MX, true>(A, K, W, A_scales, W_scales, M, N, K, epi, s);
+            return launch_mode<EPI_GELU_MX, true>(0, A, K, W, A_scales, W_scales, M, N, K, epi, s);
         case EPI_RESID_LN_MX:
             // whole 64-column wave blocks (two scale bytes per row and wave)
             if (epi.ldr % 4 != 0 || N > kResidLnMaxN || N % 64 != 0 || epi.ln_ldo % 64 != 0 ||
                 epi.ln_ldo < N || !epi.ln_gain || !epi.ln_shift || !epi.ln_out || !epi.ln_scales)
                 return hipErrorInvalidValue;
-            return launch_mode<EPI_RESID_LN_MX, true>(A, K, W, A_scales, W_scales, M, N, K, epi, s);
+            return launch_mode<EPI_RESID_LN_MX, true>(0, A, K, W, A_scales, W_scales, M, N, K, epi, s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -503,37 +525,38 @@ bool separate_layernorm(int64_t M, int N, int K) {
 
 // bf16 models: fp16 projection operands on the matrix cores.  Which tile is
 // fastest depends on how its count fills the device (every choice gives the
-// same bits); us per launch at the lines, d 512 unless said:
-//  * 64 x 64 tiles while they all run at once, two to a compute unit (4000
-//    rows x 512, K 512, 504 tiles: 7.5 against 9.5 on 64 x 256 tiles; at
-//    1000 tiles 12.2 against 11.7);
-//  * 256 x 256 tiles (k_gemm_mfma) once they fill the device, unless the
-//    last of their waves of tiles is so empty that 128 x 128 tiles, which
-//    run at 80-85% of their rate when full, lose less (16000 x 1536: 378
-//    tiles, 36 against 34; 8000 x 2048: 256 tiles, 22 against 26).  The
-//    residual update keeps them whatever the fill (30000 x 768, K 768: 61
-//    against 67: its epilogue overlaps the next MFMAs);
-//  * between the two 128 x 128 tiles as soon as some compute units get two
-//    (8000 x 1536, 756 tiles: 20 against 25), else 64 x 256 tiles (8000 x
-//    512, K 2048, 252 tiles of 128: 26 against 32).
+// same bits).
+//  * 64 x 64 tiles (k_gemm_small.hip) while they all run at once, two to a
+//    compute unit: 4000 rows x 512, K 512, 504 tiles: 7.3 us against 10 on
+//    the best of the others; 3000 x 768, K 3072, 564 tiles: 38 against 31.5.
+//  * Otherwise 256-column tiles of 64 to 256 rows, one to a compute unit,
+//    that run in rounds of as many tiles as there are compute units.  A round
+//    of 256-row tiles takes 1, of lower ones about 0.80, 0.60 and 0.42 (K
+//    4096: 118, 83, 70, 44 us; K 512: 20, 16.9, 11.2, 8.8), however full it
+//    is, so the fewest rounds by those weights win: 13692 x 768, K 3072: one
+//    round of 216 192-row tiles 67 us, three of 64-row ones 97, 128 x 128
+//    tiles two to a compute unit 89; 3000 x 1536, K 512: one round of
+//    128-row tiles 10.6, two of 64-row ones 15.8.
 template <>
 hipError_t launch_gemm<f16, bf16>(const f16* A, int64_t lda, const f16* W, int64_t M, int N,
                                   int K, const Epilogue& epi, hipStream_t s) {
     const int64_t cus = gemm_detail::device_cus();
-    const bool whole_rows = epi.mode == EPI_RESID_LN || epi.mode == EPI_RESID_SCORE;
-    if (!whole_rows) {
-        auto tiles = [&](int b) { return ((M + b - 1) / b) * (int64_t)((N + b - 1) / b); };
-        auto fill = [](int64_t n, int64_t slots) { return (double)n / (double)((n + slots - 1) / slots * slots); };
-        int block = 0;
-        if (tiles(64) <= 2 * cus)
-            block = 64;
-        else if (tiles(256) >= cus)
-            block = epi.mode != EPI_RESID && fill(tiles(256), cus) < 0.8 * fill(tiles(128), 2 * cus) ? 128 : 0;
-        else if (tiles(128) > cus)
-            block = 128;
-        if (block != 0) return launch_gemm_small<f16, bf16>(A, lda, W, M, N, K, epi, block, s);
+    if (epi.mode == EPI_RESID_LN || epi.mode == EPI_RESID_SCORE)
+        return launch_gemm_mfma(0, A, lda, W, M, N, K, epi, s);
+    if (((M + 63) / 64) * (int64_t)((N + 63) / 64) <= 2 * cus)
+        return launch_gemm_small<f16, bf16>(A, lda, W, M, N, K, epi, 64, s);
+    constexpr double kRound[4] = {0.42, 0.60, 0.80, 1.0};
+    int best = 4;
+    double cost = 0.0;
+    for (int tm = 4; tm >= 1; --tm) {
+        const int64_t tiles = ((M + 64 * tm - 1) / (64 * tm)) * (int64_t)((N + 255) / 256);
+        const double c = (double)((tiles + cus - 1) / cus) * kRound[tm - 1];
+        if (tm == 4 || c < 0.98 * cost) {
+            best = tm;
+            cost = c;
+        }
     }
-    return launch_gemm_mfma(A, lda, W, M, N, K, epi, s);
+    return launch_gemm_mfma(best, A, lda, W, M, N, K, epi, s);
 }
 
 }  // namespace upr

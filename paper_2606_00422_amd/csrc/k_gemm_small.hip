@@ -7,8 +7,7 @@
 // nobody beside it on the compute unit.  So the block tile is small and four
 // waves take a quarter of it each: 64 x 64 for fp16, 32 x 32 for fp32 (whose
 // MFMAs run 16 times longer per K value: in a 64 x 64 block their dependent
-// chain alone takes twice as long), and 128 x 128 for either once those tiles
-// fill the device.  Every wave issues a share of the loads, straight into
+// chain alone takes twice as long), 128 x 128 for large fp32 calls.  Every wave issues a share of the loads, straight into
 // LDS, and four LDS stages of one 128-byte K-step each (two for 128 x 128,
 // where another workgroup's work covers the latency) keep three K-steps in
 // flight with a single barrier per step: wait for the own loads of step t,
@@ -345,13 +344,17 @@ hipError_t launch_small_mode(const TA* A, int64_t lda, const TA* W, int64_t M, i
                              int block, hipStream_t s) {
     const int64_t tiles = ((M + block - 1) / block) * (int64_t)((N + block - 1) / block);
     constexpr int kB = sizeof(TA) == 2 ? 64 : 32;
-    if (block == kB)
+    if (block == kB) {
         k_gemm_small<TA, TKV, MODE, kB><<<(unsigned)tiles, kSmallThreads, 0, s>>>(A, lda, W, M, N, K, epi);
-    else if (block == 128)
-        k_gemm_small<TA, TKV, MODE, 128><<<(unsigned)tiles, kSmallThreads, 0, s>>>(A, lda, W, M, N, K, epi);
-    else
-        return hipErrorInvalidValue;
-    return hipGetLastError();
+        return hipGetLastError();
+    }
+    if constexpr (sizeof(TA) == 4) {
+        if (block == 128) {
+            k_gemm_small<TA, TKV, MODE, 128><<<(unsigned)tiles, kSmallThreads, 0, s>>>(A, lda, W, M, N, K, epi);
+            return hipGetLastError();
+        }
+    }
+    return hipErrorInvalidValue;
 }
 
 }  // namespace gemm_detail

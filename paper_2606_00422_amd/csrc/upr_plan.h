@@ -158,9 +158,11 @@ template <typename TA, typename TKV>
 hipError_t launch_gemm(const TA* A, int64_t lda, const TA* W, int64_t M, int N, int K,
                        const Epilogue& epi, hipStream_t s);
 
-// fp16 MFMA GEMM (K a multiple of 64, lda a multiple of 8).  (The MXFP8
+// fp16 MFMA GEMM (K a multiple of 64, lda a multiple of 8) on 256-column
+// tiles of 64 tm rows (tm = 1 to 4), or for the whole-row modes (tm = 0) on
+// tiles of 128 or 32 rows.  (The MXFP8
 // GEMM, launch_gemm_mx, is declared with the other launchers.)
-hipError_t launch_gemm_mfma(const f16* A, int64_t lda, const f16* W, int64_t M, int N, int K,
+hipError_t launch_gemm_mfma(int tm, const f16* A, int64_t lda, const f16* W, int64_t M, int N, int K,
                             const Epilogue& epi, hipStream_t s);
 
 // Whether a residual update of M rows, [M, K] x [N, K]^T, is followed by a
@@ -168,10 +170,10 @@ hipError_t launch_gemm_mfma(const f16* A, int64_t lda, const f16* W, int64_t M, 
 // (same bits either way).
 bool separate_layernorm(int64_t M, int N, int K);
 
-// The same product on block x block tiles (k_gemm_small.hip; 128, or 64 for
-// fp16 and 32 for fp32), modes EPI_STORE, EPI_GELU, EPI_GELU_PERM (fp16),
-// EPI_RESID (acc_resid allowed) and EPI_QKV_CACHE.  A and W fp16 (K a multiple
-// of 64) or fp32 (of 32).
+// The same product on block x block tiles (k_gemm_small.hip; 64 for fp16, 32
+// or 128 for fp32), modes EPI_STORE, EPI_GELU, EPI_GELU_PERM (fp16), EPI_RESID
+// (acc_resid allowed) and EPI_QKV_CACHE.  A and W fp16 (K a multiple of 64) or
+// fp32 (of 32).
 template <typename TA, typename TKV>
 hipError_t launch_gemm_small(const TA* A, int64_t lda, const TA* W, int64_t M, int N, int K,
                              const Epilogue& epi, int block, hipStream_t s);

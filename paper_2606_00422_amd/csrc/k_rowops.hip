@@ -5,19 +5,14 @@
 // (16-byte loads, 8-byte half stores); otherwise features lane + 64 i.
 // Statistics are two-pass in fp32 over the registers: mean, then the mean
 // of squared deviations (population variance), as LayerNorm defines them.
-#include "mx.h"
-#include "upr_internal.h"
+#include "row.h"
 #include "worklist.h"
 
 namespace upr {
 
 namespace {
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
-    return v;
-}
+using namespace row_detail;
 
 template <typename T> __device__ __forceinline__ float to_f(T v) { return (float)v; }
 
@@ -31,47 +26,6 @@ __device__ __forceinline__ void load4(const T* __restrict__ p, float* v) {
 }
 
 constexpr int kRowsPerBlock = 4;     // 4 waves, one row each
-constexpr int kMaxPerLane = 16;      // d <= 1024
-
-// Per-lane feature index of register slot i.
-template <bool VEC>
-__device__ __forceinline__ int feat(int lane, int i) {
-    return VEC ? (i >> 2) * 256 + 4 * lane + (i & 3) : lane + 64 * i;
-}
-
-template <bool VEC>
-__device__ __forceinline__ void load_row(const float* __restrict__ x, int d, int lane,
-                                         float (&v)[kMaxPerLane]) {
-    const int per = d >> 6;
-    if (VEC) {
-#pragma unroll
-        for (int j = 0; j < kMaxPerLane / 4; ++j)
-            if (4 * j < per) {
-                const float4 q = *reinterpret_cast<const float4*>(x + j * 256 + 4 * lane);
-                v[4 * j] = q.x; v[4 * j + 1] = q.y; v[4 * j + 2] = q.z; v[4 * j + 3] = q.w;
-            }
-    } else {
-#pragma unroll
-        for (int i = 0; i < kMaxPerLane; ++i)
-            if (i < per) v[i] = x[lane + 64 * i];
-    }
-}
-
-// (mean, 1/sqrt(var + eps)) of the row held in v.
-__device__ __forceinline__ void row_stats(const float (&v)[kMaxPerLane], int d, float eps,
-                                          float& mu, float& rstd) {
-    const int per = d >> 6;
-    float s = 0.f;
-#pragma unroll
-    for (int i = 0; i < kMaxPerLane; ++i)
-        if (i < per) s += v[i];
-    mu = wave_sum(s) / (float)d;
-    float q = 0.f;
-#pragma unroll
-    for (int i = 0; i < kMaxPerLane; ++i)
-        if (i < per) { const float t = v[i] - mu; q = fmaf(t, t, q); }
-    rstd = 1.0f / sqrtf(wave_sum(q) / (float)d + eps);
-}
 
 // Writes LN(v) (gain/shift) for the row to out (model operand type TA).
 template <bool VEC, typename TA>
@@ -103,38 +57,6 @@ __device__ __forceinline__ void store_normed(TA* __restrict__ out, const float (
                 out[c] = (TA)keep_f32(fmaf((v[i] - mu) * rstd, gain[c], shift[c]));
             }
     }
-}
-
-// Writes LN(v) for the row as MXFP8 (fp8 projection inputs): the VEC layout
-// gives a lane four consecutive features per 256-feature group, so one
-// 32-feature block is eight consecutive lanes; codes[c] is feature c's E4M3
-// code, scales[c / 32] its block's E8M0 byte.
-__device__ __forceinline__ void store_normed_mx(uint8_t* __restrict__ codes,
-                                                uint8_t* __restrict__ scales,
-                                                const float (&v)[kMaxPerLane], int d, int lane,
-                                                float mu, float rstd,
-                                                const float* __restrict__ gain,
-                                                const float* __restrict__ shift) {
-    const int per = d >> 6;
-#pragma unroll
-    for (int j = 0; j < kMaxPerLane / 4; ++j)
-        if (4 * j < per) {
-            const int c = j * 256 + 4 * lane;
-            const float4 gq = *reinterpret_cast<const float4*>(gain + c);
-            const float4 bq = *reinterpret_cast<const float4*>(shift + c);
-            const float y0 = keep_f32(fmaf((v[4 * j] - mu) * rstd, gq.x, bq.x));
-            const float y1 = keep_f32(fmaf((v[4 * j + 1] - mu) * rstd, gq.y, bq.y));
-            const float y2 = keep_f32(fmaf((v[4 * j + 2] - mu) * rstd, gq.z, bq.z));
-            const float y3 = keep_f32(fmaf((v[4 * j + 3] - mu) * rstd, gq.w, bq.w));
-            float amax = fmaxf(fmaxf(fabsf(y0), fabsf(y1)), fmaxf(fabsf(y2), fabsf(y3)));
-            amax = fmaxf(amax, __shfl_xor(amax, 1, 64));
-            amax = fmaxf(amax, __shfl_xor(amax, 2, 64));
-            amax = fmaxf(amax, __shfl_xor(amax, 4, 64));
-            const int e = mx_block_exp(amax);
-            const float inv = mx_inv_scale(e);
-            *reinterpret_cast<uint32_t*>(codes + c) = mx_pack4(y0 * inv, y1 * inv, y2 * inv, y3 * inv);
-            if ((lane & 7) == 0) scales[c >> 5] = (uint8_t)(e + 127);
-        }
 }
 
 // g = float(x); a = LN(g)  (residual stream initialisation fused with the
@@ -250,30 +172,7 @@ __global__ __launch_bounds__(256) void k_score_head(const float* __restrict__ g,
     float v[kMaxPerLane], mu, rstd;
     load_row<VEC>(g + row * d, d, lane, v);
     row_stats(v, d, eps, mu, rstd);
-    const int per = d >> 6;
-    float acc = 0.f;
-    if (VEC) {
-#pragma unroll
-        for (int j = 0; j < kMaxPerLane / 4; ++j)
-            if (4 * j < per) {
-                const int c = j * 256 + 4 * lane;
-                const float4 gq = *reinterpret_cast<const float4*>(gain + c);
-                const float4 bq = *reinterpret_cast<const float4*>(shift + c);
-                const float4 wq = *reinterpret_cast<const float4*>(w + c);
-                acc = fmaf(fmaf((v[4 * j] - mu) * rstd, gq.x, bq.x), wq.x, acc);
-                acc = fmaf(fmaf((v[4 * j + 1] - mu) * rstd, gq.y, bq.y), wq.y, acc);
-                acc = fmaf(fmaf((v[4 * j + 2] - mu) * rstd, gq.z, bq.z), wq.z, acc);
-                acc = fmaf(fmaf((v[4 * j + 3] - mu) * rstd, gq.w, bq.w), wq.w, acc);
-            }
-    } else {
-#pragma unroll
-        for (int i = 0; i < kMaxPerLane; ++i)
-            if (i < per) {
-                const int c = lane + 64 * i;
-                acc = fmaf(fmaf((v[i] - mu) * rstd, gain[c], shift[c]), w[c], acc);
-            }
-    }
-    acc = wave_sum(acc);
+    const float acc = score_row<VEC>(v, d, lane, mu, rstd, gain, shift, w);
     if (lane == 0) scores[row] = acc + b[0];
 }
 

@@ -202,6 +202,38 @@ struct ImageBuilder {
         upr::mx_quantize_host(w.data(), rows, k, reinterpret_cast<uint8_t*>(img.data() + *codes_off),
                               reinterpret_cast<uint8_t*>(img.data() + *scales_off));
     }
+    // Fragment-order copy, for the fused MXFP8 tail, of the [N, K] codes and
+    // scales at those offsets (N a multiple of 32, K of 64): fragment (t, kk) at
+    // index t (K / 64) + kk is two runs of 64 lanes x 16 bytes, lane l taking
+    // pieces l / 32 and 2 + l / 32 of the 64 codes from 64 kk of row
+    // 32t + l % 32.  Scale dwords, one per lane, hold byte (row, block
+    // 2 kk + l / 32) of four fragments: of k-steps kk = 4g .. 4g + 3 of one t
+    // (index t ceil(K / 256) + g), or, `pairs` (FFN down: N a multiple of 64, K
+    // of 128), of t = 2w, 2w + 1 and kk = 2c, 2c + 1, byte 2 (t % 2) + kk % 2
+    // (index w (K / 128) + c).
+    void add_mx_frag(size_t codes_off, size_t scales_off, int64_t N, int64_t K, bool pairs, size_t* frag_off,
+                     size_t* dword_off) {
+        const int64_t ks = K / 64, G = (ks + 3) / 4;
+        const int64_t dwords = (pairs ? N / 64 * (K / 128) : N / 32 * G) * 64;
+        *frag_off = align(img.size());
+        *dword_off = align(*frag_off + N * K);
+        img.resize(*dword_off + dwords * 4);
+        const char* src = img.data() + codes_off;
+        const char* sc = img.data() + scales_off;
+        char* dst = img.data() + *frag_off;
+        char* dsc = img.data() + *dword_off;
+        for (int64_t t = 0; t < N / 32; ++t)
+            for (int64_t kk = 0; kk < ks; ++kk)
+                for (int l = 0; l < 64; ++l) {
+                    const int64_t row = 32 * t + l % 32;
+                    for (int p = 0; p < 2; ++p)
+                        std::memcpy(dst + (t * ks + kk) * 2048 + p * 1024 + l * 16,
+                                    src + row * K + 64 * kk + 16 * (2 * p + l / 32), 16);
+                    const int64_t dw = pairs ? t / 2 * (K / 128) + kk / 2 : t * G + kk / 4;
+                    const int64_t byte = pairs ? 2 * (t % 2) + kk % 2 : kk % 4;
+                    dsc[(dw * 64 + l) * 4 + byte] = sc[row * (K / 32) + 2 * kk + l / 32];
+                }
+    }
     // Copies the image to new device memory (*dev) or fails.
     upr_status upload(void** dev) {
         img.resize(align(img.size()));
@@ -347,11 +379,12 @@ static WorkList work_list(const upr_segments* rows, const upr_segments* hist, in
 // Candidate layers of the fp8-projection variant: the bf16 sequence with
 // MXFP8 projection operands (LayerNorms write MXFP8 directly, the attention
 // kernel encodes its fp32 output, the FFN-up GEMM writes its GELU output as
-// MXFP8).
+// MXFP8).  `scores`: the score head's output, null when action heads follow;
+// *scored: whether it is written here.
 static upr_status rank_layers_mx(const upr_model* m, const upr_kv_cache* cache,
                                  const upr_segments* hist, const bf16* cand_emb,
-                                 const upr_segments* cand, const RankPlan& p, char* ws,
-                                 hipStream_t s) {
+                                 const upr_segments* cand, float* scores, bool* scored,
+                                 const RankPlan& p, char* ws, hipStream_t s) {
     const upr_config& c = m->cfg;
     const int d = c.d_model, F = c.d_ff, H = c.n_heads, D = c.head_dim;
     const int64_t R = p.rows;
@@ -377,6 +410,10 @@ static upr_status rank_layers_mx(const upr_model* m, const upr_kv_cache* cache,
     // 64-row tiles would re-read all of W2 per 64 rows (measured 0.22 ->
     // 0.32 ms for that GEMM).
     const bool fuse = d <= kResidLnMaxN && d % 64 == 0;
+    // Calls of enough rows run everything after the attention as one kernel,
+    // the following LN1 or the score head included.
+    const int tail = m->layers[0].mx_oP ? mx_tail_tile(R, d) : 0;
+    *scored = tail != 0 && scores != nullptr;
     auto resid_epilogue = [&](const float* bias, const float* ln_g, const float* ln_b) {
         Epilogue r{};
         r.mode = ln_g != nullptr ? EPI_RESID_LN_MX : EPI_RESID;
@@ -394,7 +431,7 @@ static upr_status rank_layers_mx(const upr_model* m, const upr_kv_cache* cache,
     };
     for (int l = 0; l < c.n_layers; ++l) {
         const LayerWeights& w = m->layers[l];
-        if (l > 0)
+        if (l > 0 && tail == 0)
             UPR_LAUNCH("rank.ln1",
                        launch_layernorm_mx(g, ac, asc, R, d, w.ln1_g, w.ln1_b, c.ln_eps, s));
         Epilogue e{};
@@ -421,6 +458,33 @@ static upr_status rank_layers_mx(const upr_model* m, const upr_kv_cache* cache,
                                                             hist->offsets_dev, cand->num_users, ck, cv,
                                                             cache->capacity_rows, s));
             UPR_LAUNCH("rank.quant_o", launch_mx_quantize<float>(o32, R, d, ac, asc, s));
+        }
+        if (tail != 0) {
+            const bool last = l + 1 == c.n_layers, score = last && scores != nullptr;
+            MxTail t{};
+            t.codes = ac;
+            t.scales = asc;
+            t.g = g;
+            t.resid_src = l == 0 ? cand_emb + p.row0 * d : nullptr;
+            t.wo = w.mx_oP;
+            t.w1_off = (int)(w.mx_1P - w.mx_oP);
+            t.w2_off = (int)(w.mx_2P - w.mx_oP);
+            t.wo_s = w.mx_oPs;
+            t.w1_s = w.mx_1Ps;
+            t.w2_s = w.mx_2Ps;
+            t.bo = w.bo;
+            t.ln2_g = w.ln2_g;
+            t.ln2_b = w.ln2_b;
+            t.b1 = w.b1;
+            t.b2 = w.b2;
+            t.ln_g = !last ? m->layers[l + 1].ln1_g : score ? m->fin.lnf_g : nullptr;
+            t.ln_b = !last ? m->layers[l + 1].ln1_b : score ? m->fin.lnf_b : nullptr;
+            t.ln_eps = c.ln_eps;
+            t.score_w = m->fin.w_score;
+            t.score_b = m->fin.b_score;
+            t.scores = score ? scores : nullptr;
+            UPR_LAUNCH("rank.tail", launch_mx_tail(tail, t, R, d, F, s));
+            continue;
         }
         Epilogue r = resid_epilogue(w.bo, fuse ? w.ln2_g : nullptr, w.ln2_b);
         if (l == 0) r.resid_src = cand_emb + p.row0 * d;
@@ -688,10 +752,11 @@ static upr_status run_rank(const upr_model* m, const upr_kv_cache* cache,
     TA* o = reinterpret_cast<TA*>(ws + p.off_o);
     TA* h = reinterpret_cast<TA*>(ws + p.off_h);
     const float qscale = 1.4426950408889634f / std::sqrt((float)D);
-    bool mx_done = false;
+    bool mx_done = false, mx_scored = false;
     if constexpr (std::is_same_v<Types, Bf16Types>) {
         if (c.dtype == UPR_BF16_MXFP8) {
-            const upr_status st = rank_layers_mx(m, cache, hist, cand_emb, cand, p, ws, s);
+            const upr_status st = rank_layers_mx(m, cache, hist, cand_emb, cand,
+                                                 out.heads ? nullptr : out.scores + p.row0, &mx_scored, p, ws, s);
             if (st != UPR_OK) return st;
             mx_done = true;
         }
@@ -754,7 +819,7 @@ static upr_status run_rank(const upr_model* m, const upr_kv_cache* cache,
     }
     }  // !mx_done
     if (!out.heads) {
-        if (mx_done || !fused_layernorm<Types>(c))
+        if (!mx_scored && (mx_done || !fused_layernorm<Types>(c)))
             UPR_LAUNCH("rank.score_head",
                        launch_score_head(g, out.scores + p.row0, R, d, m->fin, c.ln_eps, s));
         return UPR_OK;
@@ -814,6 +879,7 @@ upr_status upr_model_create(const upr_config* cfg, const float* weights_host,
         bool w2_perm = false;
         float s_qkv, s_o, s_1, s_2;
         size_t mx[8];       // fp8 variant: qkv, qkv scales, o, o scales, 1, 1 scales, 2, 2 scales
+        size_t mxp[6] = {};     // fragment-order o, 1, 2, each with its scales (0: none)
     };
     const bool mx = c.dtype == UPR_BF16_MXFP8;
     std::vector<LayerOff> lo(c.n_layers);
@@ -858,6 +924,12 @@ upr_status upr_model_create(const upr_config* cfg, const float* weights_host,
             ib.add_mx(Wo, d, (int)d, &lo[l].mx[2], &lo[l].mx[3]);
             ib.add_mx(W1, F, (int)d, &lo[l].mx[4], &lo[l].mx[5]);
             ib.add_mx(W2, d, (int)F, &lo[l].mx[6], &lo[l].mx[7]);
+            if (upr::mx_tail_supported((int)d, (int)F)) {
+                size_t* const q = lo[l].mxp;
+                ib.add_mx_frag(lo[l].mx[2], lo[l].mx[3], d, d, false, &q[0], &q[1]);
+                ib.add_mx_frag(lo[l].mx[4], lo[l].mx[5], F, d, false, &q[2], &q[3]);
+                ib.add_mx_frag(lo[l].mx[6], lo[l].mx[7], d, F, true, &q[4], &q[5]);
+            }
         }
         lo[l].ln1_g = add_vec(ln1_g, d);
         lo[l].ln1_b = add_vec(ln1_b, d);
@@ -917,6 +989,15 @@ upr_status upr_model_create(const upr_config* cfg, const float* weights_host,
         w.mx_1_s = mx ? u8(lo[l].mx[5]) : nullptr;
         w.mx_2 = mx ? u8(lo[l].mx[6]) : nullptr;
         w.mx_2_s = mx ? u8(lo[l].mx[7]) : nullptr;
+        if (lo[l].mxp[0]) {
+            auto u32 = [&](size_t off) { return reinterpret_cast<const uint32_t*>(base + off); };
+            w.mx_oP = u8(lo[l].mxp[0]);
+            w.mx_oPs = u32(lo[l].mxp[1]);
+            w.mx_1P = u8(lo[l].mxp[2]);
+            w.mx_1Ps = u32(lo[l].mxp[3]);
+            w.mx_2P = u8(lo[l].mxp[4]);
+            w.mx_2Ps = u32(lo[l].mxp[5]);
+        }
     }
     m->fin.lnf_g = fp(off_lnf_g);
     m->fin.lnf_b = fp(off_lnf_b);

@@ -52,6 +52,10 @@ struct LayerWeights {
     // fp8 projection variant: the same matrices as MXFP8 (E4M3 codes
     // [out, in], E8M0 scales [out, in / 32]); null for other models
     const uint8_t *mx_qkv, *mx_qkv_s, *mx_o, *mx_o_s, *mx_1, *mx_1_s, *mx_2, *mx_2_s;
+    // Wo, W1 and W2 again in the fragment order of the fused MXFP8 tail (null
+    // when it does not take the shape)
+    const uint8_t *mx_oP = nullptr, *mx_1P = nullptr, *mx_2P = nullptr;
+    const uint32_t *mx_oPs = nullptr, *mx_1Ps = nullptr, *mx_2Ps = nullptr;
     const float* ln1_g;
     const float* ln1_b;
     const float* bqkv;      // [3d]: bq, bk, bv

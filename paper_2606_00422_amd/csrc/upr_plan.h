@@ -196,6 +196,34 @@ hipError_t launch_ffn_fused(int tile, const f16* O, const f16* WoP, const Epilog
                             const f16* W2p, const float* b1, float s1, int64_t M, int d, int F,
                             const Epilogue& epi, hipStream_t s);
 
+// Fused layer tail of the MXFP8 variant (k_mx_tail.hip): the O projection of
+// codes / scales ([M, d], [M, d / 32]), LN2, FFN, both residual updates, then
+// LN of the updated rows over codes / scales (ln_g set), the score head (with
+// ln_g, ln_b and `scores`) or neither.  wo, w1, w2 and their scale dwords in
+// the fragment order the model image builds.  The residual g goes from one
+// tail of a call to the next (same tile) in the tail's own order within the
+// rows of a whole tile; a tail without ln_g and scores leaves it in rows.
+struct MxTail {
+    uint8_t* codes;
+    uint8_t* scales;
+    float* g;
+    const void* resid_src;      // set: the first residual comes from these bf16 rows
+    const uint8_t* wo;
+    int w1_off, w2_off;         // bytes from wo to W1's and W2's fragments
+    const uint32_t *wo_s, *w1_s, *w2_s;
+    const float *bo, *ln2_g, *ln2_b, *b1, *b2;
+    const float *ln_g, *ln_b;
+    float ln_eps;
+    const float *score_w, *score_b;
+    float* scores;
+};
+constexpr int kMxTailMaxF = 8192;
+bool mx_tail_supported(int d, int F);
+// Rows of its tiles in a call of M rows: 128, 64, or 0 when the separate
+// launches are faster.  The results are the same bits.
+int mx_tail_tile(int64_t M, int d);
+hipError_t launch_mx_tail(int tile, const MxTail& t, int64_t M, int d, int F, hipStream_t s);
+
 // Builds the list of `wl` (upr_internal.h) in a launch of its own.
 hipError_t launch_attn_worklist(const WorkList& wl, hipStream_t s);
 

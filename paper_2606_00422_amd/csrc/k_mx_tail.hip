@@ -31,7 +31,14 @@
 //  * The last step stages 32 updated rows at a time in LDS and treats them as
 //    the row kernels do (row.h): one wave per row.
 //
-// @@MEASURED@@
+// Measured, 128000 rows x 512, F 2048 (1000 tiles): 485 us a layer; the four
+// launches 750.  Of a tile's 120 us about 58 are the 16 chunks (3.7 us each:
+// 2 us of MFMAs at the clock they run at; removing GELU, or weights that hit
+// the first-level cache, would save 0.25 us each) and 60 the O projection and
+// the two ends, which move 1.1 MB a tile: 5 TB/s over the chip, the rate of a
+// large copy.  Tried and slower or no faster: the two waves of a SIMD half a
+// chunk apart with three chunk buffers (3.6 us a chunk, d 256 15% slower), the
+// O projection's residual read a pass ahead (registers spill).
 #include "gemm_tile.h"
 #include "row.h"
 
@@ -580,26 +587,34 @@ __global__ __launch_bounds__(512, 1) void k_mx_tail(MxTail t, int64_t M, int F) 
                 }
         }
         lds_barrier();
+        const int row = i * 32 + 4 * wave;      // of the wave's four rows, the first
+        float v[4][row_detail::kMaxPerLane];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int lr = 4 * wave + k, row = i * 32 + lr;
-            if (row >= rows) break;
-            float v[row_detail::kMaxPerLane], mu, rstd;
-            row_detail::load_row<true>(st + lr * L::kEndLd, KD, lane, v);
-            if constexpr (END == kEndPlain) {
+        for (int k = 0; k < 4; ++k) row_detail::load_row<true>(st + (4 * wave + k) * L::kEndLd, KD, lane, v[k]);
+        if constexpr (END == kEndPlain) {
 #pragma unroll
-                for (int j = 0; j < KD / 256; ++j)
-                    *reinterpret_cast<float4*>(t.g + (m0 + row) * KD + j * 256 + 4 * lane) =
-                        make_float4(v[4 * j], v[4 * j + 1], v[4 * j + 2], v[4 * j + 3]);
-                continue;
-            }
+            for (int k = 0; k < 4; ++k)
+                if (row + k < rows) {
+#pragma unroll
+                    for (int j = 0; j < KD / 256; ++j)
+                        *reinterpret_cast<float4*>(t.g + (m0 + row + k) * KD + j * 256 + 4 * lane) =
+                            make_float4(v[k][4 * j], v[k][4 * j + 1], v[k][4 * j + 2], v[k][4 * j + 3]);
+                }
+        } else {
+            float mu[4], rstd[4];
             row_detail::row_stats(v, KD, t.ln_eps, mu, rstd);
             if constexpr (END == kEndLn) {
-                row_detail::store_normed_mx(t.codes + (m0 + row) * KD, t.scales + (m0 + row) * (KD / 32), v, KD, lane,
-                                            mu, rstd, t.ln_g, t.ln_b);
-            } else if constexpr (END == kEndScore) {
-                const float s = row_detail::score_row<true>(v, KD, lane, mu, rstd, t.ln_g, t.ln_b, t.score_w);
-                if (lane == 0) t.scores[m0 + row] = s + t.score_b[0];
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    row_detail::store_normed_mx(t.codes + (m0 + row + k) * KD, t.scales + (m0 + row + k) * (KD / 32),
+                                                v[k], KD, lane, mu[k], rstd[k], t.ln_g, t.ln_b, row + k < rows);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const float s =
+                        row_detail::score_row<true>(v[k], KD, lane, mu[k], rstd[k], t.ln_g, t.ln_b, t.score_w);
+                    if (lane == 0 && row + k < rows) t.scores[m0 + row + k] = s + t.score_b[0];
+                }
             }
         }
     }
@@ -623,10 +638,16 @@ bool mx_tail_supported(int d, int F) {
     return (d == 256 || d == 512) && F > 0 && F % mx_tail_detail::kFC == 0 && F <= kMxTailMaxF;
 }
 
+// us per layer, separate launches / 64-row / 128-row tiles (F = 4d):
+//   d 256: 2000 rows 39 / 30 / 51, 8000 45 / 33 / 53, 16000 74 / 37 / 55, 20000 103 / 62 / 56
+//   d 512: 2000 rows 55 / 58 / 100, 4000 63 / 60 / 101, 8000 73 / 61 / 102, 16000 126 / 72 / 105, 20000 172 / 123 / 108
+// A tile takes about the same time however few of them run: 64-row tiles from
+// 4 (d 256) or 16 rows per compute unit, 128-row tiles once 64-row tiles would
+// need a second round.
 int mx_tail_tile(int64_t M, int d) {
     const int64_t cus = gemm_detail::device_cus();
-    (void)d;
-    return M > 64 * cus ? 128 : M > 32 * cus ? 64 : 0;
+    if (M > 64 * cus) return 128;
+    return M > cus * (d == 256 ? 4 : 16) ? 64 : 0;
 }
 
 hipError_t launch_mx_tail(int tile, const MxTail& t, int64_t M, int d, int F, hipStream_t s) {

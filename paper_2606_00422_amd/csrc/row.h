@@ -17,6 +17,14 @@ __device__ __forceinline__ float wave_sum(float v) {
     return v;
 }
 
+template <int N>
+__device__ __forceinline__ void wave_sum(float (&v)[N]) {
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1)
+#pragma unroll
+        for (int k = 0; k < N; ++k) v[k] += __shfl_xor(v[k], m, 64);
+}
+
 constexpr int kMaxPerLane = 16;      // d <= 1024
 
 // Per-lane feature index of register slot i.
@@ -43,20 +51,37 @@ __device__ __forceinline__ void load_row(const float* __restrict__ x, int d, int
     }
 }
 
-// (mean, 1/sqrt(var + eps)) of the row held in v.
-__device__ __forceinline__ void row_stats(const float (&v)[kMaxPerLane], int d, float eps,
-                                          float& mu, float& rstd) {
+// (mean, 1/sqrt(var + eps)) of the N rows held in v, their sums side by side.
+template <int N>
+__device__ __forceinline__ void row_stats(const float (&v)[N][kMaxPerLane], int d, float eps, float (&mu)[N],
+                                          float (&rstd)[N]) {
     const int per = d >> 6;
-    float s = 0.f;
+    float s[N];
 #pragma unroll
-    for (int i = 0; i < kMaxPerLane; ++i)
-        if (i < per) s += v[i];
-    mu = wave_sum(s) / (float)d;
-    float q = 0.f;
+    for (int k = 0; k < N; ++k) {
+        s[k] = 0.f;
 #pragma unroll
-    for (int i = 0; i < kMaxPerLane; ++i)
-        if (i < per) { const float t = v[i] - mu; q = fmaf(t, t, q); }
-    rstd = 1.0f / sqrtf(wave_sum(q) / (float)d + eps);
+        for (int i = 0; i < kMaxPerLane; ++i)
+            if (i < per) s[k] += v[k][i];
+    }
+    wave_sum(s);
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        mu[k] = s[k] / (float)d;
+        s[k] = 0.f;
+#pragma unroll
+        for (int i = 0; i < kMaxPerLane; ++i)
+            if (i < per) { const float t = v[k][i] - mu[k]; s[k] = fmaf(t, t, s[k]); }
+    }
+    wave_sum(s);
+#pragma unroll
+    for (int k = 0; k < N; ++k) rstd[k] = 1.0f / sqrtf(s[k] / (float)d + eps);
+}
+__device__ __forceinline__ void row_stats(const float (&v)[kMaxPerLane], int d, float eps, float& mu, float& rstd) {
+    float m[1], r[1];
+    row_stats(reinterpret_cast<const float (&)[1][kMaxPerLane]>(v), d, eps, m, r);
+    mu = m[0];
+    rstd = r[0];
 }
 
 // Writes LN(v) for the row as MXFP8 (fp8 projection inputs): the VEC layout
@@ -68,7 +93,7 @@ __device__ __forceinline__ void store_normed_mx(uint8_t* __restrict__ codes,
                                                 const float (&v)[kMaxPerLane], int d, int lane,
                                                 float mu, float rstd,
                                                 const float* __restrict__ gain,
-                                                const float* __restrict__ shift) {
+                                                const float* __restrict__ shift, bool store = true) {
     const int per = d >> 6;
 #pragma unroll
     for (int j = 0; j < kMaxPerLane / 4; ++j)
@@ -86,7 +111,9 @@ __device__ __forceinline__ void store_normed_mx(uint8_t* __restrict__ codes,
             amax = fmaxf(amax, __shfl_xor(amax, 4, 64));
             const int e = mx_block_exp(amax);
             const float inv = mx_inv_scale(e);
-            *reinterpret_cast<uint32_t*>(codes + c) = mx_pack4(y0 * inv, y1 * inv, y2 * inv, y3 * inv);
+            const uint32_t q = mx_pack4(y0 * inv, y1 * inv, y2 * inv, y3 * inv);
+            if (!store) continue;
+            *reinterpret_cast<uint32_t*>(codes + c) = q;
             if ((lane & 7) == 0) scales[c >> 5] = (uint8_t)(e + 127);
         }
 }

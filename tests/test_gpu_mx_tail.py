@@ -20,7 +20,8 @@ CASES = [
     (512, 8, 2, 128, 8192 + 64 + 63),
     (512, 8, 1, 256, 20000 // 128 * 128 + 65),
     (256, 4, 3, 1024, 16384 + 128),
-    (256, 4, 1, 128, 8192 + 1),
+    (256, 4, 1, 128, 1024 + 1),
+    (512, 8, 1, 512, 4096 + 1),
     (256, 4, 2, 256, 33000),
 ]
 
@@ -35,7 +36,7 @@ def test_tail_gives_the_bits_of_the_separate_launches(case):
     run.rank()
     ref = run.scores_np().copy()
     assert np.all(np.isfinite(ref))
-    for lo, hi in ((0, 200), (top // 2, top // 2 + 1000), (top - 300, top)):
+    for lo, hi in ((0, 200), (top // 2, min(top, top // 2 + 1000)), (top - 300, top)):
         say(f"[gpu] mx tail d={d} F={F}: rows {lo}..{hi}")
         run.scores.fill_(float("nan"))
         run.rank(coff=np.array([lo, hi], np.int32))

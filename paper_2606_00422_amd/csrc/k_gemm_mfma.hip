@@ -425,7 +425,7 @@ hipError_t launch_mode(int tm, const void* A, int64_t lda, const void* W, const 
     // 128 x 512 stages fill the LDS and leave no room for their scales.
     constexpr int kTall = (MX && Shape<MODE, 4>::kWide) ? 2 : 4;
     const int64_t tall = tile_count<MODE, kTall>(M, N);
-    if constexpr (!MX && !Shape<MODE, 4>::kWide) {
+    if constexpr (!Shape<MODE, 4>::kWide) {
         if (tm == 2 || tm == 3) {
             if (tm == 2)
                 k_gemm_mfma<MODE, MX, 2><<<(unsigned)tile_count<MODE, 2>(M, N), kThreads, 0, s>>>(A, lda, W, As, Ws, M, N, K, epi);
@@ -483,6 +483,27 @@ hipError_t launch_gemm_mfma(int tm, const f16* A, int64_t lda, const f16* W, int
     }
 }
 
+// Height of 256-column tiles (in 64 rows) for an [M, N] product: the fewest
+// rounds by their weights (launch_gemm<f16, bf16> has fp16's figures).  MXFP8
+// tiles of 64 to 256 rows against 64 or 256 only: 12000 x 768, K 3072: 56 us
+// against 87; 6000 x 2304, K 768: 21 against 33; 32000 x 768, K 3072: 116
+// against 134.
+static int tile_height(int64_t M, int N) {
+    const int64_t cus = gemm_detail::device_cus();
+    constexpr double kRound[4] = {0.42, 0.60, 0.80, 1.0};
+    int best = 4;
+    double cost = 0.0;
+    for (int tm = 4; tm >= 1; --tm) {
+        const int64_t tiles = ((M + 64 * tm - 1) / (64 * tm)) * (int64_t)((N + 255) / 256);
+        const double c = (double)((tiles + cus - 1) / cus) * kRound[tm - 1];
+        if (tm == 4 || c < 0.98 * cost) {
+            best = tm;
+            cost = c;
+        }
+    }
+    return best;
+}
+
 hipError_t launch_gemm_mx(const uint8_t* A, const uint8_t* A_scales, const uint8_t* W,
                           const uint8_t* W_scales, int64_t M, int N, int K, const Epilogue& epi,
                           hipStream_t s) {
@@ -493,13 +514,13 @@ hipError_t launch_gemm_mx(const uint8_t* A, const uint8_t* A_scales, const uint8
     switch (epi.mode) {
         case EPI_STORE:
             if (epi.ldo % 8 != 0 || epi.scale_cols % 4 != 0) return hipErrorInvalidValue;
-            return launch_mode<EPI_STORE, true>(0, A, K, W, A_scales, W_scales, M, N, K, epi, s);
+            return launch_mode<EPI_STORE, true>(tile_height(M, N), A, K, W, A_scales, W_scales, M, N, K, epi, s);
         case EPI_RESID:
             if (epi.ldr % 4 != 0) return hipErrorInvalidValue;
-            return launch_mode<EPI_RESID, true>(0, A, K, W, A_scales, W_scales, M, N, K, epi, s);
+            return launch_mode<EPI_RESID, true>(tile_height(M, N), A, K, W, A_scales, W_scales, M, N, K, epi, s);
         case EPI_GELU_MX:
             if (N % 64 != 0 || epi.ldo % 64 != 0 || !epi.out_scales) return hipErrorInvalidValue;
-            return launch_mode<EPI_GELU_MX, true>(0, A, K, W, A_scales, W_scales, M, N, K, epi, s);
+            return launch_mode<EPI_GELU_MX, true>(tile_height(M, N), A, K, W, A_scales, W_scales, M, N, K, epi, s);
         case EPI_RESID_LN_MX:
             // whole 64-column wave blocks (two scale bytes per row and wave)
             if (epi.ldr % 4 != 0 || N > kResidLnMaxN || N % 64 != 0 || epi.ln_ldo % 64 != 0 ||
@@ -545,18 +566,7 @@ hipError_t launch_gemm<f16, bf16>(const f16* A, int64_t lda, const f16* W, int64
         return launch_gemm_mfma(0, A, lda, W, M, N, K, epi, s);
     if (((M + 63) / 64) * (int64_t)((N + 63) / 64) <= 2 * cus)
         return launch_gemm_small<f16, bf16>(A, lda, W, M, N, K, epi, 64, s);
-    constexpr double kRound[4] = {0.42, 0.60, 0.80, 1.0};
-    int best = 4;
-    double cost = 0.0;
-    for (int tm = 4; tm >= 1; --tm) {
-        const int64_t tiles = ((M + 64 * tm - 1) / (64 * tm)) * (int64_t)((N + 255) / 256);
-        const double c = (double)((tiles + cus - 1) / cus) * kRound[tm - 1];
-        if (tm == 4 || c < 0.98 * cost) {
-            best = tm;
-            cost = c;
-        }
-    }
-    return launch_gemm_mfma(best, A, lda, W, M, N, K, epi, s);
+    return launch_gemm_mfma(tile_height(M, N), A, lda, W, M, N, K, epi, s);
 }
 
 }  // namespace upr

@@ -2,7 +2,8 @@
 enough rows and as separate launches in smaller ones: the same candidates get
 the same bits either way, whichever tile a row falls in (whole tiles keep the
 residual in another order than the call's last, partial one), before the
-score head and before action heads."""
+score head and before action heads.  Nor does the height of a projection's
+tile change a bit."""
 import numpy as np
 import pytest
 import torch
@@ -58,3 +59,20 @@ def test_tail_before_action_heads():
         run.coff_d = torch.from_numpy(run.coff).to("cuda")
         got = np.asarray(_run_actions(run, hb, C, Fh, uw)[0])
         assert np.array_equal(got[lo:hi], ref[lo:hi]), f"rows {lo}..{hi}"
+
+
+def test_mx_tile_height_does_not_change_scores():
+    """Projections on 256-column tiles of 64, 128, 192 or 256 rows by the size
+    of the call (d = 768: no tail), last tiles partial: the same bits."""
+    d, H, L, F, top = 768, 12, 1, 896, 33000
+    inp = make_inputs([37], [top], d, H, L, F, dtype="bf16", seed=830, variant="perturbed")
+    run = GpuRun(inp, model_dtype="bf16_mxfp8")
+    run.encode()
+    run.rank()
+    ref = run.scores_np().copy()
+    assert np.all(np.isfinite(ref))
+    for lo, hi in ((5, 6), (63, 390), (100, 4100), (7, 6107), (1000, 13011), (11, 22000)):
+        say(f"[gpu] mx tiles d={d} F={F}: rows {lo}..{hi}")
+        run.scores.fill_(float("nan"))
+        run.rank(coff=np.array([lo, hi], np.int32))
+        assert np.array_equal(run.scores_np()[lo:hi], ref[lo:hi]), f"rows {lo}..{hi}"

@@ -223,16 +223,21 @@ struct ImageBuilder {
         char* dst = img.data() + *frag_off;
         char* dsc = img.data() + *dword_off;
         for (int64_t t = 0; t < N / 32; ++t)
-            for (int64_t kk = 0; kk < ks; ++kk)
-                for (int l = 0; l < 64; ++l) {
-                    const int64_t row = 32 * t + l % 32;
-                    for (int p = 0; p < 2; ++p)
-                        std::memcpy(dst + (t * ks + kk) * 2048 + p * 1024 + l * 16,
-                                    src + row * K + 64 * kk + 16 * (2 * p + l / 32), 16);
-                    const int64_t dw = pairs ? t / 2 * (K / 128) + kk / 2 : t * G + kk / 4;
-                    const int64_t byte = pairs ? 2 * (t % 2) + kk % 2 : kk % 4;
-                    dsc[(dw * 64 + l) * 4 + byte] = sc[row * (K / 32) + 2 * kk + l / 32];
+            for (int64_t kk = 0; kk < ks; ++kk) {
+                char* const d = dst + (t * ks + kk) * 2048;
+                const int64_t dw = pairs ? t / 2 * (K / 128) + kk / 2 : t * G + kk / 4;
+                char* const ds = dsc + dw * 256 + (pairs ? 2 * (t % 2) + kk % 2 : kk % 4);
+                for (int r = 0; r < 32; ++r) {          // row 32t + r: lanes r and r + 32
+                    const char* const q = src + (32 * t + r) * K + 64 * kk;
+                    std::memcpy(d + r * 16, q, 16);
+                    std::memcpy(d + 512 + r * 16, q + 16, 16);
+                    std::memcpy(d + 1024 + r * 16, q + 32, 16);
+                    std::memcpy(d + 1536 + r * 16, q + 48, 16);
+                    const char* const b = sc + (32 * t + r) * (K / 32) + 2 * kk;
+                    ds[4 * r] = b[0];
+                    ds[4 * (r + 32)] = b[1];
                 }
+            }
     }
     // Copies the image to new device memory (*dev) or fails.
     upr_status upload(void** dev) {

@@ -71,8 +71,9 @@ typedef enum { UPR_F32 = 0, UPR_BF16 = 1, UPR_BF16_MXFP8 = 2 } upr_dtype;
  * 1 <= n_layers <= 64.  dtype selects the storage type of tokens and cache
  * and the arithmetic of the model:
  *   UPR_F32:  fp32 throughout.
- *   UPR_BF16: tokens, the K/V cache, queries/keys/values and softmax
- *             probabilities are bf16 (attention contractions are bf16 MFMA);
+ *   UPR_BF16: tokens, the K/V cache and queries/keys/values are bf16
+ *             (attention contractions are bf16 MFMA); softmax probabilities
+ *             are bf16 at head_dim 64 and fp32 at head_dim 32;
  *             the operands of the projection GEMMs (LayerNorm outputs,
  *             attention output, FFN hidden, weights) are fp16 (fp16 MFMA,
  *             same peak rate, 3 more significand bits); the residual stream,

@@ -38,7 +38,7 @@
 // no LayerNorm'd model produces); a work item whose sums come out non-finite
 // is redone exactly: a first pass finds each query's maximum logit, and the
 // second runs against it.  Row sums use v_dot2 over the bf16 probabilities,
-// the same values that weight V.
+// the same values that weight V (head_dim 32: fp32 probabilities in both).
 #include "mx.h"
 #include "upr_plan.h"
 #include "worklist.h"
@@ -122,15 +122,14 @@ __device__ __forceinline__ float quad_sum(float v) {
 // projection variant; else fp16.  kW: waves per workgroup, four, or eight
 // for ranking over long histories (256-candidate items, two workgroups per
 // CU, so still four waves per SIMD).
-// kD: head_dim.  At 32 the probabilities weight V as two bf16 terms, p = hi +
-// lo (hi the rounded p, lo the rounded rest: 16 significand bits), two MFMAs
-// and two row-sum dot products instead of one: such models have always had
-// fp32 probabilities, and one bf16 term would round them 2^8 times coarser
-// than this.  The extra MFMAs are cheap there (two 16-row blocks of V
-// instead of four); the kernel is bound by the exponentials and conversions.
-// Ranking 16 users x (32-512 rows, 200-1500 candidates), 8 heads of 32:
-// 0.321 ms per layer on the one-wave-per-row kernel, 0.0175 here; scores as
-// far from a 64-bit result as before (1.8e-3).
+// kD: head_dim.  At 32 the probabilities stay fp32, as such models have always
+// had them: they weight V as the sum of three bf16 terms, which is exact (each
+// term takes the next 8 significand bits), and the row sum adds them in fp32.
+// The extra MFMAs are cheap there (two 16-row blocks of V instead of four);
+// the kernel is bound by the exponentials and conversions.  Ranking 16 users x
+// (32-512 rows, 200-1500 candidates), 8 heads of 32, 2 layers: 807 us per call
+// on the one-wave-per-row kernel, 148 here (141 with two terms, which are 16
+// bits); scores as far from a 64-bit result as before (1.5e-3).
 template <bool CAUSAL, int kQG, bool MXO = false, int kW = 4, int kD = 64>
 __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4)) void k_attn_mfma(
     const bf16* __restrict__ qsrc, int64_t qstride, void* __restrict__ out,
@@ -140,7 +139,7 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
     // stage do not alias the loads filling the other.
     constexpr int kKS = stage_keys(kD), kES = kD / 32, kEB = kD / 16;
     constexpr int kCR = kD / 8;         // 16-byte chunks per row
-    constexpr bool kSplitP = kD == 32;
+    constexpr bool kSplitP = kD == 32;      // fp32 probabilities
     static_assert(kD == 64 || (kD == 32 && !MXO), "head_dim 64 or 32; MXFP8 output at 64 only");
     __shared__ __attribute__((aligned(16))) bf16 sK0[kKS * kD];
     __shared__ __attribute__((aligned(16))) bf16 sK1[kKS * kD];
@@ -340,26 +339,55 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
     };
     // probabilities, row sums and O^T += V^T P^T of a sub-block
     auto weigh = [&](const bf16* cV, int kb, const f32x4 (&s)[kQG][2], const b8* ahead) __attribute__((always_inline)) {
-        b8 pf[kQG], pl[kQG];                // probabilities (kSplitP: hi and lo)
+        if constexpr (kSplitP) {
+            // p = p0 + p1 + p2, exactly; one group of queries at a time (the
+            // terms of both would not fit the registers of four waves per SIMD)
+            b8 vf[kEB];
+#pragma unroll
+            for (int eb = 0; eb < kEB; ++eb) {
+                if constexpr (kReadAhead)
+                    vf[eb] = ahead[eb];
+                else
+                    vf[eb] = read_v(cV, kb, eb);
+            }
+#pragma unroll
+            for (int qg = 0; qg < kQG; ++qg) {
+                b8 p0, p1, p2;
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float p = fast_exp2(s[qg][t][r]);
+                        l[qg] += p;
+                        p0[t * 4 + r] = (__bf16)p;
+                        const float rest = p - (float)p0[t * 4 + r];
+                        p1[t * 4 + r] = (__bf16)rest;
+                        p2[t * 4 + r] = (__bf16)(rest - (float)p1[t * 4 + r]);
+                    }
+                prio(high{});
+#pragma unroll
+                for (int eb = 0; eb < kEB; ++eb) {
+                    o[qg][eb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[eb], p0, o[qg][eb], 0, 0, 0);
+                    o[qg][eb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[eb], p1, o[qg][eb], 0, 0, 0);
+                    o[qg][eb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[eb], p2, o[qg][eb], 0, 0, 0);
+                }
+                prio(low{});
+                if (qg + 1 < kQG) __builtin_amdgcn_sched_barrier(0);
+            }
+            return;
+        }
+        b8 pf[kQG];
 #pragma unroll
         for (int qg = 0; qg < kQG; ++qg) {
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float p = fast_exp2(s[qg][t][r]);
-                    pf[qg][t * 4 + r] = (__bf16)p;
-                    if constexpr (kSplitP) pl[qg][t * 4 + r] = (__bf16)(p - (float)pf[qg][t * 4 + r]);
-                }
+                for (int r = 0; r < 4; ++r) pf[qg][t * 4 + r] = (__bf16)fast_exp2(s[qg][t][r]);
             const b2 ones = {(__bf16)1.0f, (__bf16)1.0f};
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const b2 pp = {pf[qg][2 * j], pf[qg][2 * j + 1]};
                 l[qg] = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, l[qg], false);
-                if constexpr (kSplitP) {
-                    const b2 pq = {pl[qg][2 * j], pl[qg][2 * j + 1]};
-                    l[qg] = __builtin_amdgcn_fdot2_f32_bf16(pq, ones, l[qg], false);
-                }
             }
         }
         prio(high{});
@@ -371,11 +399,8 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
             else
                 vf = read_v(cV, kb, eb);
 #pragma unroll
-            for (int qg = 0; qg < kQG; ++qg) {
+            for (int qg = 0; qg < kQG; ++qg)
                 o[qg][eb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pf[qg], o[qg][eb], 0, 0, 0);
-                if constexpr (kSplitP)
-                    o[qg][eb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, pl[qg], o[qg][eb], 0, 0, 0);
-            }
         }
         prio(low{});
     };

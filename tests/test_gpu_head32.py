@@ -4,8 +4,10 @@ the oracle at the edges of its tiles (32-key sub-blocks, 128-key stages,
 the same bits."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
+from paper_2606_00422_amd import upr
 from synth import make_inputs
 
 from .gpu_util import GpuRun, assert_cache_match, assert_scores_match, say
@@ -70,3 +72,48 @@ def test_exact_redo(monkeypatch):
     ref = oracle.rank(inp.weights, 128, 4, 1, 256, run.cache_np(), inp.hist_offsets, inp.cand_emb,
                       inp.cand_offsets)
     assert_scores_match(got, ref, "head32 exact redo, on the GPU's cache", scale=2.0)
+
+
+def test_probabilities_weigh_values_in_fp32(monkeypatch):
+    """Two history keys of nearly equal logits with opposite values A: the
+    attention output A (p0 - p1) / (1 + p0 + p1) is the probabilities' error
+    but for 2^-13 of A, and fp16 storage keeps 11 bits of that.  The rank call
+    is stopped after the attention (UPR_STOP_AFTER) and its output compared
+    with float64 on the GPU's own queries."""
+    d, H, D, F, R, A = 64, 2, 32, 64, 700, 1024.0
+    rng = np.random.default_rng(630)
+    zero, eye = np.zeros, np.eye(d, dtype=np.float32)
+    blob = [np.ones(d), zero(d), eye / 8, zero(d), zero((d, d)), zero(d), zero((d, d)), zero(d),     # LN1, Wq, Wk, Wv
+            eye, zero(d), np.ones(d), zero(d), zero((F, d)), zero(F), zero((d, F)), zero(d),         # Wo, LN2, W1, W2
+            np.ones(d), zero(d), np.ones(d), zero(1)]
+    cfg = upr.make_config(d, H, 1, F, "bf16")
+    model = upr.Model(cfg, np.concatenate([np.ravel(x) for x in blob]).astype(np.float32))
+    cache = model.new_cache(2)
+    k0 = torch.from_numpy(rng.uniform(0.07, 0.12, (H, D)).astype(np.float32)).to(torch.bfloat16)
+    k1 = k0.clone()
+    k1[:, ::8] += 2.0 ** -11                    # one or two units of bf16 in four of 32 values
+    cache[0, 0, :, 0], cache[0, 0, :, 1] = k0.cuda(), k1.cuda()
+    cache[0, 1, :, 0], cache[0, 1, :, 1] = A, -A
+    hoff, coff = np.array([0, 2], np.int32), np.array([0, R], np.int32)
+    hd, cd = torch.from_numpy(hoff).cuda(), torch.from_numpy(coff).cuda()
+    X = torch.from_numpy(rng.standard_normal((R, d)).astype(np.float32)).cuda().to(torch.bfloat16)
+    scores = torch.empty(R, dtype=torch.float32, device="cuda")
+    ws = model.workspace(upr.upr_rank_workspace_bytes(model.handle, upr.segments(hoff, hd), upr.segments(coff, cd)))
+    monkeypatch.setenv("UPR_STOP_AFTER", "3")   # LayerNorm and work list, q|k|v, attention
+    model.rank(cache, hoff, hd, X, coff, cd, scores, ws=ws)
+    torch.cuda.synchronize()
+    at = R * d * 4 + R * d * 2                  # past the residual and LN1 (whole 256-byte blocks)
+    assert R * d % 128 == 0
+    q = ws[at:at + R * 3 * d * 2].view(torch.bfloat16).double().cpu().reshape(R, 3, H, D)[:, 0]
+    at += R * 3 * d * 2
+    o = ws[at:at + R * d * 2].view(torch.float16).double().cpu().reshape(R, H, D)
+    p0, p1 = (torch.exp2((q * k.double()).sum(-1)) for k in (k0, k1))
+    ref = (A * (p0 - p1) / (1 + p0 + p1))[..., None]
+    # logits: sums of 32 products, below 0.5 in all, at 2^-24 a rounding; the
+    # exponential another 2^-23: 2^-22 of A for the pair with room to spare.
+    # (Two bf16 terms per probability leave up to 2^-18 of it.)
+    err = (o - ref).abs()
+    bound = A * 2.0 ** -22 + ref.abs() * 2.0 ** -11
+    assert ref.abs().max() < A * 2.0 ** -9
+    say(f"[gpu] head32 probabilities: worst error {float((err / A).max()):.2e} of A, of the bound {float((err / bound).max()):.2f}")
+    assert bool((err <= bound).all())

@@ -45,16 +45,6 @@ __device__ __forceinline__ float quad_sum(float v) {
     return v + __shfl_xor(v, 32, 64);
 }
 
-// Wait states between an MFMA and the first VALU read of its result, spelled
-// out where a branch lies between the two: this compiler (ROCm 7.2) counts
-// them along the taken path only there, and the fall-through read logits that
-// were not yet written (a running maximum that differed from run to run).
-__device__ __forceinline__ void mfma_settled() {
-    __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_nop 15");
-    __builtin_amdgcn_sched_barrier(0);
-}
-
 // qsrc: ranking, q|k|v rows (stride 3d); encode, query rows (stride d, own
 // keys in the cache).  Queries are pre-scaled by log2(e)/sqrt(D).
 template <bool CAUSAL, int D>
@@ -153,7 +143,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(const float* __restrict__ q
 #pragma unroll
             for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_mfma_f32_16x16x4f32(k[i], q[c][i], s, 0, 0, 0);
         }
-        mfma_settled();
+        mfma_settled<16>();
         if (__builtin_expect(CAUSAL ? kabs + 15 > ipos0 + qg * 16 : kabs + 16 > n, 0)) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
@@ -206,7 +196,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(const float* __restrict__ q
     }
     if (st < nst) stage(sK0, sV0, sK1, sV1, st);
 
-    mfma_settled();
+    mfma_settled<16>();
     // ---- key half 1 hands its state to half 0 through LDS (all reads of the
     // stages ended at the last barrier)
     float* const x = sK0 + qg * (64 * (4 * kEB + 2));

@@ -475,6 +475,7 @@ __global__ __launch_bounds__(512, 1) void k_mx_tail(MxTail t, int64_t M, int F) 
             if (i == kUT - 1) refill(s);
             __builtin_amdgcn_sched_barrier(0);
         }
+        mfma_settled<20>();         // (a refill's choice of address may be a branch)
 #pragma unroll
         for (int i = 0; i < kUT; ++i) asm volatile("" : "+v"(hacc[i]));
         char* const hb = sH + (c & 1) * kRows * kFC;

@@ -87,6 +87,23 @@ __device__ __forceinline__ float keep_f32(float x) {
     return x;
 }
 
+// kStates wait states between an MFMA and the first other instruction that
+// touches its result, spelled out where a branch lies between the two: this
+// compiler (ROCm 7.2) counts them along the longer path only there, and on the
+// other a result was read before it was written (a running maximum that
+// differed from run to run).  v_mfma_f32_16x16x4_f32 takes 10, the scaled
+// 32x32x64 one 20.  tests/test_mfma_wait_states.py walks the built kernels.
+template <int kStates>
+__device__ __forceinline__ void mfma_settled() {
+    static_assert(kStates > 0 && kStates <= 32, "two s_nop");
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (kStates <= 16)
+        asm volatile("s_nop %0" ::"n"(kStates - 1));
+    else
+        asm volatile("s_nop 15\n\ts_nop %0" ::"n"(kStates - 17));
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // Epilogue modes of the projection GEMMs, out = A W^T + bias, then:
 enum EpiMode : int {
     EPI_STORE = 0,      // out[m, n] (kv type); columns < scale_cols are multiplied by col_scale

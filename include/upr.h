@@ -168,6 +168,11 @@ size_t upr_rank_workspace_bytes(const upr_model* model, const upr_segments* hist
  * For each user and layer l, the causal transformer (position t attends to
  * positions 0..t of the same user) writes that layer's keys and values of the
  * user's rows into cache plane l.  Only those cache rows are written.
+ * An infinite or NaN token value makes its own position's cache rows
+ * non-finite and may make later positions' of its user so; positions before
+ * it are unaffected, except in bf16 models of head_dim 64, where it may also
+ * reach the earlier positions of its block of 32 (32 j .. 32 j + 31 of the
+ * user): the mask gives it probability 0 there, and 0 times its value is NaN.
  * ws: device workspace of at least upr_encode_workspace_bytes, 256-byte
  * aligned; its contents are scratch. */
 upr_status upr_encode_user(const upr_model* model, const void* hist_emb,

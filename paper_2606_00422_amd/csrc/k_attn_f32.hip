@@ -19,7 +19,8 @@
 //
 // The softmax is exact: a running maximum per query (fp32 logits, starting
 // from the query's own logit), probabilities and sums fp32, O rescaled when
-// the maximum moves; the two key halves are merged through LDS.
+// the maximum moves; the two key halves are merged through LDS.  (The bare
+// exponential instruction: probabilities below 2^-126 of the largest are 0.)
 //
 // Bound by the fp32 matrix rate (157 TFLOP/s nominal): per 16 keys a wave
 // issues D/2 MFMAs of 32 cycles and about 60 VALU instructions.  Ranking 4
@@ -27,6 +28,7 @@
 // 175 on the one-wave-per-row kernel.
 #include <type_traits>
 
+#include "attn_row.h"
 #include "upr_plan.h"
 
 namespace upr {
@@ -209,19 +211,47 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(const float* __restrict__ q
         x[(4 * kEB + 1) * 64 + lane] = l;
     }
     __syncthreads();
-    if (kh == 1 || qg * 16 + l16 >= kc) return;
+    if (kh == 1) return;
     const float m1 = x[4 * kEB * 64 + lane];
     const float mm = fmaxf(m, m1);
     const float a0 = __builtin_amdgcn_exp2f(m - mm), a1 = __builtin_amdgcn_exp2f(m1 - mm);
     l = l * a0 + x[(4 * kEB + 1) * 64 + lane] * a1;
     const float inv = 1.0f / quad_sum(l);
+    const bool valid = qg * 16 + l16 < kc;
+    bool bad = false;
+#pragma unroll
+    for (int j = 0; j < kEB; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            o[j][r] = (o[j][r] * a0 + x[(4 * j + r) * 64 + lane] * a1) * inv;
+            bad |= nonfinite_bits(o[j][r]);
+        }
+    if constexpr (CAUSAL) {
+        // queries that a later position's infinite or NaN value may have reached
+        const unsigned long long any = __ballot(bad && valid);
+        for (int i = 0; any != 0 && i < 16; ++i) {
+            if ((any & (0x0001000100010001ull << i)) == 0) continue;
+            const int qr = qg * 16 + i;
+            const float v = causal_row<float, D>(qsrc + (c0 - row0 + qr) * qstride + h * D,
+                                                 cache_k + ((int64_t)h * cap + hb) * D,
+                                                 cache_v + ((int64_t)h * cap + hb) * D, ipos0 + qr);
+#pragma unroll
+            for (int j = 0; j < kEB; ++j)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const float e = __shfl(v, kEB * (4 * g + r) + j, 64);
+                    if (l16 == i) o[j][r] = e;
+                }
+        }
+    }
+    if (!valid) return;
     float* const orow = out + (c0 - row0 + qi) * d + h * D + 4 * kEB * g;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         typedef std::conditional_t<D == 64, f32x4, f32x2> vrow;
         vrow v;
 #pragma unroll
-        for (int j = 0; j < kEB; ++j) v[j] = (o[j][r] * a0 + x[(4 * j + r) * 64 + lane] * a1) * inv;
+        for (int j = 0; j < kEB; ++j) v[j] = o[j][r];
         *reinterpret_cast<vrow*>(orow + kEB * r) = v;
     }
 }

@@ -39,6 +39,7 @@
 // is redone exactly: a first pass finds each query's maximum logit, and the
 // second runs against it.  Row sums use v_dot2 over the bf16 probabilities,
 // the same values that weight V (head_dim 32: fp32 probabilities in both).
+#include "attn_row.h"
 #include "mx.h"
 #include "upr_plan.h"
 #include "worklist.h"
@@ -88,10 +89,8 @@ template <int D> __device__ __forceinline__ int key_v(int row) {
 
 __device__ __forceinline__ float max3(float a, float b, float c) { return fmaxf(a, fmaxf(b, c)); }
 
-// Inf or NaN, tested on the bits (this file is built without NaN semantics).
-__device__ __forceinline__ bool nonfinite(float x) {
-    return (__float_as_uint(x) & 0x7f800000u) == 0x7f800000u;
-}
+// (NaN is no overflow, and this file is built without NaN semantics.)
+__device__ __forceinline__ bool is_inf(float x) { return __builtin_fabsf(x) == INFINITY; }
 
 // 2^x on the transcendental unit (-inf gives 0; 2^128 and above give inf).
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -467,11 +466,11 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
     bool bad = force_exact != 0;
 #pragma unroll
     for (int qg = 0; qg < kQG; ++qg) {
-        bad |= nonfinite(l[qg]);
+        bad |= is_inf(l[qg]);
 #pragma unroll
         for (int eb = 0; eb < kEB; ++eb)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) bad |= nonfinite(o[qg][eb][r]);
+            for (int r = 0; r < 4; ++r) bad |= is_inf(o[qg][eb][r]);
     }
     if (__syncthreads_or(bad)) {
         float mref[kQG];
@@ -506,6 +505,37 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
         }
         init_state(mref);
         run();
+    }
+
+    // ---- queries that a later position's infinite or NaN value may have
+    // reached, through sums that multiply it by zero.  (At head_dim 64 they
+    // stay: those models have always run on this kernel alone, and the
+    // registers of its 32-query waves are all taken.)
+    if constexpr (CAUSAL && kD == 32) {
+#pragma unroll
+        for (int qg = 0; qg < kQG; ++qg) {
+            const int q0 = wave * kQW + qg * 16;
+            bool lost = false;
+#pragma unroll
+            for (int eb = 0; eb < kEB; ++eb)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) lost |= nonfinite_bits(o[qg][eb][r]);
+            const unsigned long long any = __ballot(lost && q0 + l16 < kc);
+            for (int i = 0; any != 0 && i < 16; ++i) {
+                if ((any & (0x0001000100010001ull << i)) == 0) continue;
+                const float v = causal_row<bf16, kD>(qsrc + (c0 - row0 + q0 + i) * qstride + h * kD,
+                                                     cache_k + ((int64_t)h * cap + hb) * kD,
+                                                     cache_v + ((int64_t)h * cap + hb) * kD, ipos0 + q0 + i);
+#pragma unroll
+                for (int eb = 0; eb < kEB; ++eb)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float e = __shfl(v, 16 * eb + 4 * g + r, 64);
+                        if (l16 == i) o[qg][eb][r] = e;
+                    }
+                if (l16 == i) l[qg] = g == 0 ? 1.f : 0.f;           // normalised already
+            }
+        }
     }
 
     // ---- normalise and store (lane holds e = 16eb + 4g + r of query l16)

@@ -50,6 +50,42 @@ def test_history_change_leaves_earlier_rows_bit_identical(u, t):
     assert not np.array_equal(c1[0, :, :, row, :], c0[0, :, :, row, :])
 
 
+# fp32 models, and bf16 ones of head_dim 32 on 64-row and on 128-row items
+@pytest.mark.parametrize("dt,lens,d,H,F", [("f32", [300, 77, 513, 0], 256, 4, 512),
+                                           ("f32", [300, 77], 128, 4, 256),
+                                           ("bf16", [300, 77, 513, 0], 128, 4, 256),
+                                           ("bf16", [150, 140] * 32, 256, 8, 256)])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_a_non_finite_token_stays_behind_the_causal_mask(dt, lens, d, H, F, bad):
+    """One bad value in a late token: that user's cache rows before it, at every
+    layer and in both planes, are what they are without it; the token's own
+    rows are not finite; other users' rows keep their bits."""
+    L = 3
+    inp = make_inputs(lens, [1] * len(lens), d, H, L, F, dtype=dt, seed=47, variant="perturbed")
+    base = GpuRun(inp)
+    base.encode()
+    c0 = base.cache_np()
+    ho = inp.hist_offsets
+    for u, t in ((0, 149), (1, 17), (0, 128), (1, 31)):
+        say(f"[gpu] causality: {bad} in user {u} position {t}, {dt} d={d} H={H}")
+        first, row = int(ho[u]), int(ho[u]) + t
+        run = GpuRun(inp)
+        run.X[row, 5] = bad
+        run.encode()
+        c1 = run.cache_np()
+        assert not np.any(np.isfinite(c1[0, :, :, row]))
+        before, want = c1[:, :, :, first:row], c0[:, :, :, first:row]
+        lost = np.argwhere(~np.isfinite(before))
+        assert lost.size == 0, f"first at (layer, kv, head, position, e) = {lost[0]}"
+        # the same sums in another order: fp32 roundings (bf16 models: and an
+        # occasional bf16 rounding the other way, as assert_cache_match allows)
+        tol = 1e-4 if dt == "f32" else 2e-2 * L
+        assert np.abs(before - want).max() <= tol * (1 + np.abs(want).max())
+        keep = np.ones(c0.shape[3], bool)
+        keep[first:int(ho[u + 1])] = False
+        assert np.array_equal(c1[:, :, :, keep], c0[:, :, :, keep])
+
+
 def test_ranking_never_writes_the_cache():
     import torch
     inp = _inp()

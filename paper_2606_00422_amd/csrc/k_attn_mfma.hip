@@ -35,10 +35,11 @@
 // accumulated as they are (fp32 sums, bf16 probabilities: relative precision
 // does not depend on magnitude), and the normaliser uses the same reference.
 // Only overflow can go wrong (a logit about 2^7 above its reference, a range
-// no LayerNorm'd model produces); a work item whose sums come out non-finite
-// is redone exactly: a first pass finds each query's maximum logit, and the
-// second runs against it.  Row sums use v_dot2 over the bf16 probabilities,
-// the same values that weight V (head_dim 32: fp32 probabilities in both).
+// no LayerNorm'd model produces); a work item whose sums overflow (or at
+// head_dim 32 come near it) is redone exactly: a first pass finds each query's
+// maximum logit, and the second runs against it.  Row sums use v_dot2 over the
+// bf16 probabilities, the same values that weight V (head_dim 32: fp32
+// probabilities in both).
 #include "attn_row.h"
 #include "mx.h"
 #include "upr_plan.h"
@@ -466,7 +467,9 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
     bool bad = force_exact != 0;
 #pragma unroll
     for (int qg = 0; qg < kQG; ++qg) {
-        bad |= is_inf(l[qg]);
+        // (kSplitP: the row sum is fp32, but a probability's first bf16 term
+        // overflows before fp32 does, and its terms then add up to NaN in o)
+        bad |= kSplitP ? l[qg] >= 0x1p100f : is_inf(l[qg]);
 #pragma unroll
         for (int eb = 0; eb < kEB; ++eb)
 #pragma unroll

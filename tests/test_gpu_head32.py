@@ -74,39 +74,48 @@ def test_exact_redo(monkeypatch):
     assert_scores_match(got, ref, "head32 exact redo, on the GPU's cache", scale=2.0)
 
 
-def test_probabilities_weigh_values_in_fp32(monkeypatch):
-    """Two history keys of nearly equal logits with opposite values A: the
-    attention output A (p0 - p1) / (1 + p0 + p1) is the probabilities' error
-    but for 2^-13 of A, and fp16 storage keeps 11 bits of that.  The rank call
-    is stopped after the attention (UPR_STOP_AFTER) and its output compared
-    with float64 on the GPU's own queries."""
-    d, H, D, F, R, A = 64, 2, 32, 64, 700, 1024.0
-    rng = np.random.default_rng(630)
-    zero, eye = np.zeros, np.eye(d, dtype=np.float32)
-    blob = [np.ones(d), zero(d), eye / 8, zero(d), zero((d, d)), zero(d), zero((d, d)), zero(d),     # LN1, Wq, Wk, Wv
-            eye, zero(d), np.ones(d), zero(d), zero((F, d)), zero(F), zero((d, F)), zero(d),         # Wo, LN2, W1, W2
+def _attention_of(monkeypatch, Wq, bq, X, K, V):
+    """Attention output [R, H, D] (float64) of a one-layer d 64 model with 32-value
+    heads, query projection Wq, bq and no key or value of a candidate's own
+    (own logit 0, own value 0), for candidates X over one user's history K, V
+    [H, n, D], and the queries it used.  The rank call is stopped after the
+    attention (UPR_STOP_AFTER)."""
+    d, H, D, F, R, n = 64, 2, 32, 64, X.shape[0], K.shape[1]
+    zero = np.zeros
+    blob = [np.ones(d), zero(d), Wq, bq, zero((d, d)), zero(d), zero((d, d)), zero(d),                  # LN1, Wq, Wk, Wv
+            np.eye(d), zero(d), np.ones(d), zero(d), zero((F, d)), zero(F), zero((d, F)), zero(d),      # Wo, LN2, W1, W2
             np.ones(d), zero(d), np.ones(d), zero(1)]
-    cfg = upr.make_config(d, H, 1, F, "bf16")
-    model = upr.Model(cfg, np.concatenate([np.ravel(x) for x in blob]).astype(np.float32))
-    cache = model.new_cache(2)
-    k0 = torch.from_numpy(rng.uniform(0.07, 0.12, (H, D)).astype(np.float32)).to(torch.bfloat16)
-    k1 = k0.clone()
-    k1[:, ::8] += 2.0 ** -11                    # one or two units of bf16 in four of 32 values
-    cache[0, 0, :, 0], cache[0, 0, :, 1] = k0.cuda(), k1.cuda()
-    cache[0, 1, :, 0], cache[0, 1, :, 1] = A, -A
-    hoff, coff = np.array([0, 2], np.int32), np.array([0, R], np.int32)
+    model = upr.Model(upr.make_config(d, H, 1, F, "bf16"),
+                      np.concatenate([np.ravel(x) for x in blob]).astype(np.float32))
+    cache = model.new_cache(n)
+    cache[0, 0], cache[0, 1] = K.cuda(), V.cuda()
+    hoff, coff = np.array([0, n], np.int32), np.array([0, R], np.int32)
     hd, cd = torch.from_numpy(hoff).cuda(), torch.from_numpy(coff).cuda()
-    X = torch.from_numpy(rng.standard_normal((R, d)).astype(np.float32)).cuda().to(torch.bfloat16)
     scores = torch.empty(R, dtype=torch.float32, device="cuda")
     ws = model.workspace(upr.upr_rank_workspace_bytes(model.handle, upr.segments(hoff, hd), upr.segments(coff, cd)))
     monkeypatch.setenv("UPR_STOP_AFTER", "3")   # LayerNorm and work list, q|k|v, attention
-    model.rank(cache, hoff, hd, X, coff, cd, scores, ws=ws)
+    model.rank(cache, hoff, hd, X.cuda(), coff, cd, scores, ws=ws)
     torch.cuda.synchronize()
-    at = R * d * 4 + R * d * 2                  # past the residual and LN1 (whole 256-byte blocks)
-    assert R * d % 128 == 0
+    assert R * d % 128 == 0                     # whole 256-byte blocks: no gaps between
+    at = R * d * 4 + R * d * 2                  # past the residual and LN1
     q = ws[at:at + R * 3 * d * 2].view(torch.bfloat16).double().cpu().reshape(R, 3, H, D)[:, 0]
     at += R * 3 * d * 2
-    o = ws[at:at + R * d * 2].view(torch.float16).double().cpu().reshape(R, H, D)
+    return ws[at:at + R * d * 2].view(torch.float16).double().cpu().reshape(R, H, D), q
+
+
+def test_probabilities_weigh_values_in_fp32(monkeypatch):
+    """Two history keys of nearly equal logits with opposite values A: the
+    attention output A (p0 - p1) / (1 + p0 + p1) is the probabilities' error
+    but for 2^-13 of A, and fp16 storage keeps 11 bits of that.  Against
+    float64 on the GPU's own queries."""
+    d, H, D, R, A = 64, 2, 32, 700, 1024.0
+    rng = np.random.default_rng(630)
+    k0 = torch.from_numpy(rng.uniform(0.07, 0.12, (H, D)).astype(np.float32)).to(torch.bfloat16)
+    k1 = k0.clone()
+    k1[:, ::8] += 2.0 ** -11                    # one or two units of bf16 in four of 32 values
+    V = torch.tensor([A, -A], dtype=torch.bfloat16)[None, :, None].expand(H, 2, D)
+    X = torch.from_numpy(rng.standard_normal((R, d)).astype(np.float32)).to(torch.bfloat16)
+    o, q = _attention_of(monkeypatch, np.eye(d) / 8, np.zeros(d), X, torch.stack([k0, k1], 1), V)
     p0, p1 = (torch.exp2((q * k.double()).sum(-1)) for k in (k0, k1))
     ref = (A * (p0 - p1) / (1 + p0 + p1))[..., None]
     # logits: sums of 32 products, below 0.5 in all, at 2^-24 a rounding; the
@@ -117,3 +126,20 @@ def test_probabilities_weigh_values_in_fp32(monkeypatch):
     assert ref.abs().max() < A * 2.0 ** -9
     say(f"[gpu] head32 probabilities: worst error {float((err / A).max()):.2e} of A, of the bound {float((err / bound).max()):.2f}")
     assert bool((err <= bound).all())
+
+
+@pytest.mark.parametrize("excess", [[120, 0.5], [127, 0.875], [127, 0.99609375, 0.00244140625], [127, 2], [127, 127]])
+def test_logits_far_above_the_own(monkeypatch, excess):
+    """A history logit up to 2^128 and more above the candidate's own, which the
+    softmax takes as its reference: just below where the probability overflows
+    as bf16, between that and fp32's largest, and beyond.  The history's value
+    takes all of the weight."""
+    d, H, D, R = 64, 2, 32, 4
+    K = torch.zeros(H, 3, D, dtype=torch.bfloat16)
+    K[:, 1, :len(excess)] = torch.tensor(excess, dtype=torch.bfloat16)
+    V = torch.tensor([1.0, 3.0, -2.0], dtype=torch.bfloat16)[None, :, None].expand(H, 3, D)
+    bq = np.full(d, np.sqrt(32) * np.log(2))    # queries of 1 (pre-scaled by log2(e) / sqrt(32))
+    o, q = _attention_of(monkeypatch, np.zeros((d, d)), bq, torch.zeros(R, d, dtype=torch.bfloat16), K, V)
+    assert bool((q == 1).all())
+    say(f"[gpu] head32 logits {sum(excess)} above the own: {o.min().item()}..{o.max().item()}")
+    assert bool((o == 3).all())

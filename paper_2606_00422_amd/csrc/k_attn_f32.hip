@@ -129,23 +129,32 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(const float* __restrict__ q
     // the diagonal key)
     const bool with_own = !CAUSAL && kh == 0;
     float l = with_own && g == 0 ? 1.f : 0.f;
-    f32x4 o[kEB];                                   // o[j][r]: e = kEB (4g + r) + j
+    // o[j][r]: e = kEB (4g + r) + j; the odd keys of a lane group in oo (two sums
+    // of half the length each, added at the end: half their rounding error)
+    f32x4 o[kEB], oo[kEB];
 #pragma unroll
     for (int j = 0; j < kEB; ++j)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) o[j][r] = with_own ? qrow[2 * d + kEB * (4 * g + r) + j] : 0.f;
+        for (int r = 0; r < 4; ++r) {
+            o[j][r] = with_own ? qrow[2 * d + kEB * (4 * g + r) + j] : 0.f;
+            oo[j][r] = 0.f;
+        }
 
     // 16 keys, rows kb .. kb + 15 of the stage, keys kabs .. of the user
     auto block = [&](const float* cK, const float* cV, int kb, int kabs) __attribute__((always_inline)) {
-        f32x4 s = {0.f, 0.f, 0.f, 0.f};
+        f32x4 s = {0.f, 0.f, 0.f, 0.f}, so = s;     // (two sums, as for o)
         const int row = kb + l16;
 #pragma unroll
         for (int c = 0; c < kC; ++c) {
             const f32x4 k = *reinterpret_cast<const f32x4*>(cK + row * D + (((4 * c + g) ^ key(row)) << 2));
 #pragma unroll
-            for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_mfma_f32_16x16x4f32(k[i], q[c][i], s, 0, 0, 0);
+            for (int i = 0; i < 4; i += 2) {
+                s = __builtin_amdgcn_mfma_f32_16x16x4f32(k[i], q[c][i], s, 0, 0, 0);
+                so = __builtin_amdgcn_mfma_f32_16x16x4f32(k[i + 1], q[c][i + 1], so, 0, 0, 0);
+            }
         }
         mfma_settled<16>();
+        s += so;
         if (__builtin_expect(CAUSAL ? kabs + 15 > ipos0 + qg * 16 : kabs + 16 > n, 0)) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
@@ -162,7 +171,10 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(const float* __restrict__ q
 #pragma unroll
             for (int j = 0; j < kEB; ++j)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) o[j][r] *= alpha;
+                for (int r = 0; r < 4; ++r) {
+                    o[j][r] *= alpha;
+                    oo[j][r] *= alpha;
+                }
         }
         float p[4];
 #pragma unroll
@@ -173,7 +185,10 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(const float* __restrict__ q
         for (int r = 0; r < 4; ++r) {
             const vrow v = *reinterpret_cast<const vrow*>(cV + (kb + 4 * g + r) * D + kEB * l16);
 #pragma unroll
-            for (int j = 0; j < kEB; ++j) o[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[j], p[r], o[j], 0, 0, 0);
+            for (int j = 0; j < kEB; ++j) {
+                f32x4& sum = r & 1 ? oo[j] : o[j];
+                sum = __builtin_amdgcn_mfma_f32_16x16x4f32(v[j], p[r], sum, 0, 0, 0);
+            }
         }
     };
     const int wave_last = ipos0 + min(qg * 16 + 16, kc) - 1;    // encode: the wave's last query position
@@ -199,6 +214,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_f32(const float* __restrict__ q
     if (st < nst) stage(sK0, sV0, sK1, sV1, st);
 
     mfma_settled<16>();
+#pragma unroll
+    for (int j = 0; j < kEB; ++j) o[j] += oo[j];
     // ---- key half 1 hands its state to half 0 through LDS (all reads of the
     // stages ended at the last barrier)
     float* const x = sK0 + qg * (64 * (4 * kEB + 2));

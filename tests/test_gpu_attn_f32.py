@@ -43,6 +43,26 @@ def test_edges_match_oracle(case, variant):
     say(f"[gpu] f32 attention case {case}/{variant}: cache {err.max():.2e}, scores {e.max():.2e}")
 
 
+# (history lens, candidate lens, d, H, L, F, most): relative error (2-norm, mean of
+# four seeds) of the scores against the float64 oracle, at most what one wave
+# per row and FMA projections in sequence, the kernels these models once ran
+# on, left on the same inputs (their own roundings, not a bound on any)
+@pytest.mark.parametrize("n,k,d,H,L,F,most", [([1957], [74], 64, 1, 2, 256, 3.66e-7),
+                                              ([400, 300], [300, 500], 256, 4, 2, 1024, 1.00e-6),
+                                              ([64], [128], 64, 2, 1, 256, 4.61e-7)])
+def test_error_against_64_bits(n, k, d, H, L, F, most):
+    errors = []
+    for seed in range(840, 844):
+        inp = make_inputs(n, k, d, H, L, F, dtype="f32", seed=seed, variant="perturbed")
+        run = GpuRun(inp)
+        run.encode()
+        run.rank()
+        ref = oracle.rank(inp.weights, d, H, L, F, run.cache_np(), inp.hist_offsets, inp.cand_emb, inp.cand_offsets)
+        errors.append(np.linalg.norm(run.scores_np() - ref) / np.linalg.norm(ref))
+    say(f"[gpu] f32 error d={d} n={n}: {np.mean(errors):.3e} ({', '.join(f'{e:.2e}' for e in errors)})")
+    assert np.mean(errors) <= most
+
+
 @pytest.mark.parametrize("dt,H", [("f32", 2), ("f32", 4), ("bf16", 4)])
 def test_workspace_without_room_for_the_list(dt, H):
     """A workspace a few bytes short of the reported size, as one sized before

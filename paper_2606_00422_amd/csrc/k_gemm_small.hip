@@ -7,12 +7,12 @@
 // nobody beside it on the compute unit.  So the block tile is small and four
 // waves take a quarter of it each: 64 x 64 for fp16, 32 x 32 for fp32 (whose
 // MFMAs run 16 times longer per K value: in a 64 x 64 block their dependent
-// chain alone takes twice as long), 128 x 128 for large fp32 calls.  Every wave issues a share of the loads, straight into
-// LDS, and four LDS stages of one 128-byte K-step each (two for 128 x 128,
-// where another workgroup's work covers the latency) keep three K-steps in
-// flight with a single barrier per step: wait for the own loads of step t,
-// barrier, refill the stage that step t - 1 read, read the fragments of step
-// t, multiply those of step t - 1.  (Eight stages were no faster for any
+// chain alone takes twice as long), 128 x 128 for large fp32 calls.  Every wave
+// issues a share of the loads, straight into LDS, and four LDS stages of one
+// 128-byte K-step each (two for 128 x 128, where another workgroup's work
+// covers the latency) keep three K-steps in flight with a single barrier per
+// step: wait for the own loads of step t, barrier, refill the stage that step
+// t - 1 read, read the fragments of step t, multiply those of step t - 1.  (Eight stages were no faster for any
 // K up to 4096: the steps are bound by the LDS port, 16 KB written and 32 KB
 // read per step, and by the barrier, not by the loads' latency.)
 //
@@ -405,16 +405,26 @@ hipError_t launch_gemm_small(const TA* A, int64_t lda, const TA* W, int64_t M, i
 template hipError_t launch_gemm_small<f16, bf16>(const f16*, int64_t, const f16*, int64_t, int, int, const Epilogue&,
                                                  int, hipStream_t);
 
-// fp32 models: 128 x 128 tiles once they put two workgroups on every compute
-// unit (8000 x 1024, K 256, 504 tiles: 41 us against 50 on 32 x 32; with 378
-// tiles 37 against 35), 32 x 32 below.
+// fp32 models: 32 x 32 tiles, whose time grows with their number, or 128 x 128
+// ones, which cost less per output but run in rounds of one per compute unit.
+// Per 32 x 32 outputs the large ones take 0.88 (K + 60) / (K + 100) of the small
+// ones' time (the constants are the ends of a tile, in K values: per 1000 tiles
+// of 32 x 32, K 64: 1.8 and 2.8 us; K 256: 4.4 and 5.5; K 2048: 30 and 35), so
+// that they win where their rounds are full enough.  us, small / large: K 512,
+// 2634 x 1536 (252 large tiles) 41 / 39, 3298 x 1536 (312) 50 / 66; K 256,
+// 27456 x 256 (430) 43 / 38; K 2048, 8908 x 1024 (560) 320 / 371.  Over 150
+// shapes of 60 to 1560 large tiles the choice costs at most 9% and 0.2% on
+// average against the faster (large tiles from 504 up: 25% and 2.2%).
 template <>
 hipError_t launch_gemm<float, float>(const float* A, int64_t lda, const float* W, int64_t M, int N, int K,
                                      const Epilogue& epi, hipStream_t s) {
     if (epi.resid_src != nullptr) return hipErrorInvalidValue;      // fp32 residual rows only
+    const int64_t cus = gemm_detail::device_cus();
+    const int64_t tiles32 = ((M + 31) / 32) * (int64_t)((N + 31) / 32);
     const int64_t tiles128 = ((M + 127) / 128) * (int64_t)((N + 127) / 128);
-    const int block = tiles128 >= 2 * gemm_detail::device_cus() - 8 ? 128 : 32;
-    return launch_gemm_small<float, float>(A, lda, W, M, N, K, epi, block, s);
+    const int64_t rounds = (tiles128 + cus - 1) / cus;
+    const bool large = 0.88 * (K + 60) * 16.0 * (double)(rounds * cus) <= (double)(K + 100) * (double)tiles32;
+    return launch_gemm_small<float, float>(A, lda, W, M, N, K, epi, large ? 128 : 32, s);
 }
 
 }  // namespace upr

@@ -67,3 +67,22 @@ def test_encode_call_size_does_not_change_the_cache(dt):
         run.encode(hoff=np.array([ho[u], ho[u + 1]], np.int32))
         got = run.cache_np()
         assert np.array_equal(got[:, :, :, ho[u]:ho[u + 1]], ref[:, :, :, ho[u]:ho[u + 1]]), f"user {u}"
+
+
+def test_f32_tile_size_does_not_change_scores():
+    """fp32 projections on 128 x 128 tiles (one full round of them: 4096 rows) and
+    on 32 x 32 ones (just past the round, and small calls)."""
+    d, H, L, F, top = 320, 5, 1, 960, 4096
+    inp = make_inputs([37], [top + 1], d, H, L, F, dtype="f32", seed=730, variant="perturbed")
+    run = GpuRun(inp)
+    run.encode()
+    got = {}
+    for lo, hi in ((0, top + 1), (0, top), (1, top + 1), (100, 2000), (4000, top + 1)):
+        say(f"[gpu] f32 tiles: rows {lo}..{hi}")
+        run.scores.fill_(float("nan"))
+        run.rank(coff=np.array([lo, hi], np.int32))
+        got[lo, hi] = run.scores_np().copy()
+    ref = got[0, top + 1]
+    assert np.all(np.isfinite(ref))
+    for (lo, hi), g in got.items():
+        assert np.array_equal(g[lo:hi], ref[lo:hi]), f"rows {lo}..{hi}"

@@ -660,19 +660,25 @@ hipError_t launch_mode(int tile, const f16* O, const h8* WoP, const Epilogue& ep
 
 }  // namespace ffn_detail
 
-// us per layer tail, unfused / 64-row / 128-row tiles (F = 4d):
-//   d 128: 4000 rows 21 / 22 / 36, 8000 30 / 22 / 37, 20000 60 / 42 / 37
-//   d 256: 4000 rows 30 / 36 / 57, 8000 42 / 38 / 58, 16000 63 / 39 / 59, 20000 81 / 74 / 61
-//   d 512: 8000 rows 73 / 84 / 116, 10000 100 / 86 / 119, 16000 128 / 95 / 126, 24000 191 / 172 / 132
-// A tail tile takes about the same time however few of them run, the unfused
-// sequence grows with the rows: 64-row tiles from 16 (d 128) to 32 rows per
-// compute unit (d >= 384), 128-row tiles once 64-row tiles would need a second
-// round.
-int ffn_fused_tile(int64_t M, int d) {
+// us per layer of a ranking call over a short history, unfused / 64-row tiles:
+//   d 128: F 256: 700 rows 34 / 26, 3000 31 / 27; F 512: 2500 30 / 31, 5000 38 / 33; F 1024: 4000 40 / 41, 6000 47 / 43
+//   d 256: F 256: 3000 37 / 38, 5000 45 / 41; F 512: 4000 42 / 44, 5500 52 / 47; F 1024: 6500 58 / 58, 8256 70 / 58
+//   d 384: F 384: 8000 60 / 60, 8256 86 / 64; F 1536: 8192 84 / 96, 8256 106 / 98; F 3072: 8192 115 / 142, 8256 146 / 144
+//   d 512: F 512: 4000 54 / 56, 4500 63 / 58; F 1024: 6000 76 / 77, 8000 86 / 82; F 4096: 8192 156 / 183, 8256 197 / 186
+// A tail tile takes about the same time however few of them run, more with F;
+// the unfused sequence grows with the rows and steps up where its 64 x 64
+// tiles need another round, above all at 32 rows per compute unit.  So 64-row
+// tiles from a number of rows per compute unit that grows with F, 32 at most (at
+// d 384, where the unfused tiles fit best, always).  128-row tiles once 64-row
+// ones would need a second round (F = 4d, 64-row / 128-row tail alone: d 256,
+// 20000 rows 74 / 61; d 512, 24000 172 / 132).
+int ffn_fused_tile(int64_t M, int d, int F) {
     const int64_t cus = gemm_detail::device_cus();
     if (M > 64 * cus) return 128;
-    const int per_cu = 8 + d / 16 < 32 ? 8 + d / 16 : 32;
-    return M > cus * per_cu ? 64 : 0;
+    int64_t from = 32 * cus;
+    if (d == 128) from = std::min(from, cus * F / 50);
+    if (d == 256 || d == 512) from = std::min(from, 9 * cus + cus * F / 60);
+    return M > from ? 64 : 0;
 }
 
 bool ffn_fused_supported(int d, int F) {

@@ -639,16 +639,20 @@ bool mx_tail_supported(int d, int F) {
     return (d == 256 || d == 512) && F > 0 && F % mx_tail_detail::kFC == 0 && F <= kMxTailMaxF;
 }
 
-// us per layer, separate launches / 64-row / 128-row tiles (F = 4d):
-//   d 256: 2000 rows 39 / 30 / 51, 8000 45 / 33 / 53, 16000 74 / 37 / 55, 20000 103 / 62 / 56
-//   d 512: 2000 rows 55 / 58 / 100, 4000 63 / 60 / 101, 8000 73 / 61 / 102, 16000 126 / 72 / 105, 20000 172 / 123 / 108
-// A tile takes about the same time however few of them run: 64-row tiles from
-// 4 (d 256) or 16 rows per compute unit, 128-row tiles once 64-row tiles would
-// need a second round.
-int mx_tail_tile(int64_t M, int d) {
+// us per layer of a ranking call over a short history, separate launches /
+// 64-row tiles:
+//   d 256: F 256: 500 rows 35 / 30; F 1024: 1300 44 / 38; F 2048: 2000 50 / 51, 3000 55 / 53
+//   d 512: F 512: 700 48 / 51, 1500 50 / 46; F 1024: 3000 58 / 61, 4500 64 / 59; F 2048: 5500 79 / 81, 7000 88 / 82;
+//          F 4096: 6000 109 / 113, 7000 119 / 116
+// A tile takes about the same time however few of them run, more with F:
+// 64-row tiles from a number of rows per compute unit that grows with F, 25 at
+// most; 128-row tiles once 64-row tiles would need a second round (F = 4d, tail
+// alone, 64-row / 128-row: d 256, 20000 rows 62 / 56; d 512, 20000 123 / 108).
+int mx_tail_tile(int64_t M, int d, int F) {
     const int64_t cus = gemm_detail::device_cus();
     if (M > 64 * cus) return 128;
-    return M > cus * (d == 256 ? 4 : 16) ? 64 : 0;
+    const int64_t from = d == 256 ? std::max(2 * cus, cus * F / 256) : std::max(4 * cus, std::min(25 * cus, cus * F / 72));
+    return M > from ? 64 : 0;
 }
 
 hipError_t launch_mx_tail(int tile, const MxTail& t, int64_t M, int d, int F, hipStream_t s) {

@@ -417,7 +417,7 @@ static upr_status rank_layers_mx(const upr_model* m, const upr_kv_cache* cache,
     const bool fuse = d <= kResidLnMaxN && d % 64 == 0;
     // Calls of enough rows run everything after the attention as one kernel,
     // the following LN1 or the score head included.
-    const int tail = m->layers[0].mx_oP ? mx_tail_tile(R, d) : 0;
+    const int tail = m->layers[0].mx_oP ? mx_tail_tile(R, d, F) : 0;
     *scored = tail != 0 && scores != nullptr;
     auto resid_epilogue = [&](const float* bias, const float* ln_g, const float* ln_b) {
         Epilogue r{};
@@ -557,7 +557,7 @@ static hipError_t launch_ffn_block(const char* const names[7], const upr_config&
     // the layer's tail in one kernel (O projection, residual update, LN2,
     // FFN with its hidden rows on chip, then the next LayerNorm or the score
     // head) for calls with enough rows for its tiles
-    const int tail_tile = ffn_fused_tile(R, d);
+    const int tail_tile = ffn_fused_tile(R, d, F);
     const bool tail = std::is_same_v<Types, Bf16Types> && fuse && w.WoP != nullptr && w.W1p != nullptr &&
                       (next_g != nullptr || scores != nullptr) && tail_tile != 0;
     const bool sep_o = fuse && !tail && separate_layernorm(R, d, d);

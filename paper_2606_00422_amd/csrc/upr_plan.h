@@ -191,7 +191,7 @@ bool ffn_fused_supported(int d, int F);
 // Rows of the fused kernel's tiles in a call of M rows: 128, 64, or 0 when
 // the call runs the unfused sequence on small tiles, which is faster for few
 // rows.  The results are the same bits (same products in the same order).
-int ffn_fused_tile(int64_t M, int d);
+int ffn_fused_tile(int64_t M, int d, int F);
 hipError_t launch_ffn_fused(int tile, const f16* O, const f16* WoP, const Epilogue& epa, const f16* W1p,
                             const f16* W2p, const float* b1, float s1, int64_t M, int d, int F,
                             const Epilogue& epi, hipStream_t s);
@@ -221,7 +221,7 @@ constexpr int kMxTailMaxF = 8192;
 bool mx_tail_supported(int d, int F);
 // Rows of its tiles in a call of M rows: 128, 64, or 0 when the separate
 // launches are faster.  The results are the same bits.
-int mx_tail_tile(int64_t M, int d);
+int mx_tail_tile(int64_t M, int d, int F);
 hipError_t launch_mx_tail(int tile, const MxTail& t, int64_t M, int d, int F, hipStream_t s);
 
 // Builds the list of `wl` (upr_internal.h) in a launch of its own.

@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
 CASES = [
     (64, 1, 2, 64, "bf16", 20000),
     (320, 5, 1, 576, "bf16", 20000),        # no fused tail: whole-row tiles
-    (128, 2, 1, 384, "bf16", 33000),        # fused tails from 4,097 rows up
+    (128, 2, 1, 384, "bf16", 33000),        # fused tails on 64-row tiles from 1,967 rows up
     (256, 4, 2, 512, "bf16", 33000),
     (512, 8, 1, 1024, "bf16", 33000),
     (768, 12, 1, 832, "bf16", 9000),        # rows past the whole-row tile

@@ -266,9 +266,10 @@ upr_status check_workspace(void* ws, size_t ws_bytes, size_t need) {
 }
 
 // The plan make(true), or make(false), without a work list where one is
-// optional, if only that fits `have` bytes.
+// optional, if only that fits `have` bytes or `lists` is false.
 template <typename Make>
-auto fit_plan(const Make& make, size_t have) {
+auto fit_plan(const Make& make, size_t have, bool lists) {
+    if (!lists) return make(false);
     auto p = make(true);
     if (p.bytes > have) {
         auto q = make(false);
@@ -276,6 +277,11 @@ auto fit_plan(const Make& make, size_t have) {
     }
     return p;
 }
+
+// Whether the matrix-core attention can read the cache: it loads rows in
+// 16-byte pieces.  (fp32 models and head_dim 32 have a kernel that reads single
+// values; head_dim 64 of bf16 has always asked for aligned rows.)
+bool wide_loads(const upr_kv_cache* cache) { return reinterpret_cast<uintptr_t>(cache->data) % 16 == 0; }
 
 #define UPR_HIP(...)                                                                            \
     do {                                                                                        \
@@ -1063,7 +1069,8 @@ upr_status upr_encode_user(const upr_model* m, const void* hist_emb, const upr_s
         return fail(UPR_ERR_CAPACITY, "history rows end at %lld, cache capacity is %lld",
                     (long long)last, (long long)cache->capacity_rows);
     const upr::EncodePlan p = fit_plan(
-        [&](bool lists) { return upr::plan_encode(m->cfg, hist->num_users, hist->offsets_host, lists); }, ws_bytes);
+        [&](bool lists) { return upr::plan_encode(m->cfg, hist->num_users, hist->offsets_host, lists); }, ws_bytes,
+        wide_loads(cache));
     st = check_workspace(ws, ws_bytes, p.bytes);
     if (st != UPR_OK) return st;
     if (p.rows == 0) return ok();
@@ -1107,7 +1114,7 @@ static upr_status rank_entry(const upr_model* m, const upr_kv_cache* cache,
         [&](bool lists) {
             return upr::plan_rank(m->cfg, cand->num_users, cand->offsets_host, hist->offsets_host, 0, lists);
         },
-        scratch ? UPR_NOALLOC_SCRATCH_BYTES : ws_bytes);
+        scratch ? UPR_NOALLOC_SCRATCH_BYTES : ws_bytes, wide_loads(cache));
     if (scratch) {
         if (p.bytes > UPR_NOALLOC_SCRATCH_BYTES)
             return fail(UPR_ERR_LIMIT, "the call needs a %zu-byte workspace; the no-alloc scratch "
@@ -1263,7 +1270,7 @@ upr_status upr_rank_actions(const upr_model* m, const upr_heads* hd, const upr_k
             return upr::plan_rank(m->cfg, cand->num_users, cand->offsets_host, hist->offsets_host, hd->C * hd->Fh,
                                   lists);
         },
-        ws_bytes);
+        ws_bytes, wide_loads(cache));
     st = check_workspace(ws, ws_bytes, p.bytes);
     if (st != UPR_OK) return st;
     if (p.rows == 0) return ok();

@@ -68,7 +68,8 @@ inline int64_t attn_items(const upr_config& c, int U, const int32_t* offs, int t
 //    MXFP8 output covers whole 64-value heads), and
 //  * where the list does not fit (`lists` false): a workspace that held these
 //    calls before they had a list still does.  (bf16 encode at head_dim 64
-//    then takes its larger items, whose list is half as long.)
+//    then takes its larger items, whose list is half as long.)  `lists` is
+//    also false for a cache off the 16-byte boundaries of the kernels' loads.
 inline bool use_mfma_attn(const upr_config& c, bool rank, int U, const int32_t* hoffs, bool lists) {
     if (bf16_storage(c) && c.head_dim == 64) return true;
     if (!lists || (rank && c.dtype == UPR_BF16_MXFP8)) return false;

@@ -91,3 +91,32 @@ def test_workspace_without_room_for_the_list(dt, H):
     with pytest.raises(upr.UprError):
         run.model.rank(run.cache, run.hoff, run.hoff_d, run.C, run.coff, run.coff_d, run.scores,
                        ws=torch.empty(short, dtype=torch.uint8, device="cuda"))
+
+
+@pytest.mark.parametrize("dt,H", [("f32", 2), ("f32", 4), ("bf16", 4)])
+def test_cache_off_the_16_byte_boundaries(dt, H):
+    """A cache 4 bytes past a 16-byte boundary runs on the kernels that read
+    single values, in encode and in ranking: the bits of a call whose workspace
+    has no room for the work list."""
+    import torch
+    d, L, F = 128, 2, 256
+    inp = make_inputs([70, 0, 129], [130, 5, 64], d, H, L, F, dtype=dt, seed=821, variant="perturbed")
+    run = GpuRun(inp)
+    hs, cs = upr.segments(run.hoff, run.hoff_d), upr.segments(run.coff, run.coff_d)
+    need = upr.upr_rank_workspace_bytes(run.model.handle, hs, cs)
+    enc = upr.upr_encode_workspace_bytes(run.model.handle, hs)
+    run.model.encode(run.X, run.hoff, run.hoff_d, run.cache, ws=run.model.workspace(enc - 1))
+    run.model.rank(run.cache, run.hoff, run.hoff_d, run.C, run.coff, run.coff_d, run.scores,
+                   ws=run.model.workspace(need - 1))
+    want, want_cache = run.scores_np().copy(), run.cache_np().copy()
+    assert np.all(np.isfinite(want))
+    off = 1 if dt == "f32" else 2
+    flat = torch.zeros(run.cache.numel() + 16, dtype=run.cache.dtype, device="cuda")
+    run.cache = flat[off:off + run.cache.numel()].view(run.cache.shape)
+    assert run.cache.data_ptr() % 16 == 4
+    run.scores.fill_(float("nan"))
+    run.encode()
+    run.rank()
+    assert np.array_equal(run.cache_np(), want_cache)
+    assert np.array_equal(run.scores_np(), want)
+    assert not flat[:off].any() and not flat[off + run.cache.numel():].any()

@@ -4,7 +4,6 @@
 // applies a wave's 128 x 64 (or 32 x 64) accumulator tile to its outputs.
 #pragma once
 
-#include "epilogue.h"
 #include "mx.h"
 #include "upr_plan.h"
 

@@ -263,14 +263,15 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
 
     // One 32-key sub-block (keys kb .. kb+31 of the stage in cK / cV).
     typedef b8 KFrag[2][kES];               // [16-key half][32-value step]
-    auto read_k = [&](const bf16* cK, int kb, KFrag& kf) __attribute__((always_inline)) {
+    // the lane's key row `row` of the stage, values 32 es + 8g .. + 7
+    auto read_k = [&](const bf16* cK, int row, int es) __attribute__((always_inline)) {
+        return *reinterpret_cast<const b8*>(&cK[row * kD + (((es * 4 + g) ^ key_k<kD>(row)) << 3)]);
+    };
+    auto read_k_block = [&](const bf16* cK, int kb, KFrag& kf) __attribute__((always_inline)) {
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int row = kb + t * 16 + l16;
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int es = 0; es < kES; ++es)
-                kf[t][es] = *reinterpret_cast<const b8*>(&cK[row * kD + (((es * 4 + g) ^ key_k<kD>(row)) << 3)]);
-        }
+            for (int es = 0; es < kES; ++es) kf[t][es] = read_k(cK, kb + t * 16 + l16, es);
     };
     // V^T fragment of e-block eb: lane (g, i) needs V[key(8g + j)][16eb + i];
     // in each 16-lane group, lane s of a transposing read addresses row
@@ -306,13 +307,12 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             b8 kf[kES];
-            const int row = kb + t * 16 + l16;
 #pragma unroll
             for (int es = 0; es < kES; ++es) {
                 if constexpr (kReadAhead)
                     kf[es] = (*ahead)[t][es];
                 else
-                    kf[es] = *reinterpret_cast<const b8*>(&cK[row * kD + (((es * 4 + g) ^ key_k<kD>(row)) << 3)]);
+                    kf[es] = read_k(cK, kb + t * 16 + l16, es);
             }
 #pragma unroll
             for (int qg = 0; qg < kQG; ++qg) {
@@ -420,7 +420,7 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
             // before its arithmetic
             if (wave_active && !(CAUSAL && k0 > wave_last)) {
                 KFrag kf[2];
-                read_k(cK, 0, kf[0]);
+                read_k_block(cK, 0, kf[0]);
 #pragma unroll
                 for (int i = 0; i < kKS / 32; ++i) {
                     const int kabs = k0 + 32 * i;
@@ -428,7 +428,7 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
                     b8 vf[kEB];
 #pragma unroll
                     for (int eb = 0; eb < kEB; ++eb) vf[eb] = read_v(cV, 32 * i, eb);
-                    if (i + 1 < kKS / 32) read_k(cK, 32 * i + 32, kf[(i + 1) & 1]);
+                    if (i + 1 < kKS / 32) read_k_block(cK, 32 * i + 32, kf[(i + 1) & 1]);
                     f32x4 s[kQG][2];
                     logits(cK, 32 * i, kabs, s, &kf[i & 1]);
                     weigh(cV, 32 * i, s, vf);
@@ -485,10 +485,8 @@ __global__ __launch_bounds__(64 * kW, kW == 8 ? 2 : (8 / kQG < 4 ? 8 / kQG : 4))
             __syncthreads();
             for (int kb = 0; kb < kKS && st * kKS + kb < nkeys; kb += 16) {
                 b8 kf[kES];
-                const int row = kb + l16;
 #pragma unroll
-                for (int es = 0; es < kES; ++es)
-                    kf[es] = *reinterpret_cast<const b8*>(&sK0[row * kD + (((es * 4 + g) ^ key_k<kD>(row)) << 3)]);
+                for (int es = 0; es < kES; ++es) kf[es] = read_k(sK0, kb + l16, es);
 #pragma unroll
                 for (int qg = 0; qg < kQG; ++qg) {
                     f32x4 acc = {0.f, 0.f, 0.f, 0.f};

@@ -293,7 +293,6 @@ __global__ __launch_bounds__(512, 1) void k_ffn_fused(const f16* __restrict__ O,
 
     // up-phase role: row tiles kUT um .., hidden columns 32 un ..
     const int um = wave >> 2, un = wave & 3;
-    constexpr bool up_on = true;
     // down-phase role: output columns 64 wave .. +63
     const bool dn_on = kD == kMaxD || wave * 64 < kD;
 
@@ -416,7 +415,7 @@ __global__ __launch_bounds__(512, 1) void k_ffn_fused(const f16* __restrict__ O,
             const int sn = s + kRing;
             if (sn < kOSteps) {
                 if (dn_on) ring[slot_o(s)] = load_o(sn);
-            } else if (up_on) {
+            } else {
                 ring[slot_o(s)] = load_w1(0, sn - kOSteps);
             }
         };
@@ -509,59 +508,53 @@ __global__ __launch_bounds__(512, 1) void k_ffn_fused(const f16* __restrict__ O,
 #pragma unroll
             for (int r = 0; r < 16; ++r) hacc[i][r] = 0.f;
         h8 af[2][kUT];
-        if (up_on) a_frags(0, af[0]);
+        a_frags(0, af[0]);
 #pragma unroll
         for (int s = 0; s < kUpSteps; ++s) {
-            if (up_on && s + 1 < kUpSteps) a_frags(s + 1, af[(s + 1) & 1]);
-            if (up_on) {
-                __builtin_amdgcn_s_setprio(1);
+            if (s + 1 < kUpSteps) a_frags(s + 1, af[(s + 1) & 1]);
+            __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-                for (int i = 0; i < kUT; ++i)
-                    hacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, ring[(base + s) % kRing]), af[s & 1][i],
-                                                                     hacc[i], 0, 0, 0);
-                __builtin_amdgcn_s_setprio(0);
-            }
+            for (int i = 0; i < kUT; ++i)
+                hacc[i] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(h8, ring[(base + s) % kRing]), af[s & 1][i],
+                                                                 hacc[i], 0, 0, 0);
+            __builtin_amdgcn_s_setprio(0);
             refill(s);
             __builtin_amdgcn_sched_barrier(0);
         }
         // lane (row, half h) holds hidden columns 32 un + 8q + 4h + s of its
         // rows; chunk b of a row tile takes q in {2b, 2b + 1}, i.e.
         // down-phase k-step 2 un + b, half h
-        if (up_on) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q)
-                bq[q] = *reinterpret_cast<const float4*>(b1 + c * kFC + 32 * un + 8 * q + 4 * lhalf);
+        for (int q = 0; q < 4; ++q)
+            bq[q] = *reinterpret_cast<const float4*>(b1 + c * kFC + 32 * un + 8 * q + 4 * lhalf);
 #pragma unroll
-            for (int i = 0; i < kUT; ++i)
+        for (int i = 0; i < kUT; ++i)
 #pragma unroll
-                for (int b = 0; b < 2; ++b)
+            for (int b = 0; b < 2; ++b)
 #pragma unroll
-                    for (int qq = 0; qq < 2; ++qq) {
-                        const int q = 2 * b + qq;
-                        const float v0 = gelu_fast(fmaf(hacc[i][4 * q + 0], s1, bq[q].x));
-                        const float v1 = gelu_fast(fmaf(hacc[i][4 * q + 1], s1, bq[q].y));
-                        const float v2 = gelu_fast(fmaf(hacc[i][4 * q + 2], s1, bq[q].z));
-                        const float v3 = gelu_fast(fmaf(hacc[i][4 * q + 3], s1, bq[q].w));
-                        pk[i][b][2 * qq] = pack2<false>(v0, v1);
-                        pk[i][b][2 * qq + 1] = pack2<false>(v2, v3);
-                    }
-        }
+                for (int qq = 0; qq < 2; ++qq) {
+                    const int q = 2 * b + qq;
+                    const float v0 = gelu_fast(fmaf(hacc[i][4 * q + 0], s1, bq[q].x));
+                    const float v1 = gelu_fast(fmaf(hacc[i][4 * q + 1], s1, bq[q].y));
+                    const float v2 = gelu_fast(fmaf(hacc[i][4 * q + 2], s1, bq[q].z));
+                    const float v3 = gelu_fast(fmaf(hacc[i][4 * q + 3], s1, bq[q].w));
+                    pk[i][b][2 * qq] = pack2<false>(v0, v1);
+                    pk[i][b][2 * qq + 1] = pack2<false>(v2, v3);
+                }
         __builtin_amdgcn_sched_barrier(0);
     };
     // the chunk's hidden values into the chunk buffer, then a barrier before
     // any wave's down phase reads them
     auto write_h = [&]() __attribute__((always_inline)) {
-        if (up_on) {
 #pragma unroll
-            for (int i = 0; i < kUT; ++i)
+        for (int i = 0; i < kUT; ++i)
 #pragma unroll
-                for (int b = 0; b < 2; ++b) {
-                    const int kkp = 2 * un + b;                 // down-phase k-step
-                    char* dst = reinterpret_cast<char*>(sH + (kkp >> 2) * kRows * 64) +
-                                ((um * kUT + i) * 32 + lrow) * 128 + choff[kkp & 3];
-                    *reinterpret_cast<u32x4*>(dst) = u32x4{pk[i][b][0], pk[i][b][1], pk[i][b][2], pk[i][b][3]};
-                }
-        }
+            for (int b = 0; b < 2; ++b) {
+                const int kkp = 2 * un + b;                 // down-phase k-step
+                char* dst = reinterpret_cast<char*>(sH + (kkp >> 2) * kRows * 64) +
+                            ((um * kUT + i) * 32 + lrow) * 128 + choff[kkp & 3];
+                *reinterpret_cast<u32x4*>(dst) = u32x4{pk[i][b][0], pk[i][b][1], pk[i][b][2], pk[i][b][3]};
+            }
         __builtin_amdgcn_s_waitcnt(0xC07F);     // lgkmcnt(0): this wave's writes are done
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();

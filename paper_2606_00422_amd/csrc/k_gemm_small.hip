@@ -67,6 +67,14 @@ template <> struct Operand<float> {
     }
 };
 
+// GELU of fp32 models.
+__device__ __forceinline__ float gelu_tanh_f(float x) {
+    // 0.5 x (1 + tanh(sqrt(2/pi) (x + 0.044715 x^3)))
+    const float k0 = 0.7978845608028654f;
+    const float y = k0 * (x + 0.044715f * x * x * x);
+    return 0.5f * x * (1.0f + tanhf(y));
+}
+
 constexpr int kSmallThreads = 256;
 
 // kB: block tile rows and columns; each of the four waves takes a quarter,

@@ -8,6 +8,7 @@ import numpy as np
 import pytest
 
 import oracle
+from paper_2606_00422_amd import upr
 from synth import make_inputs
 
 from .gpu_util import ATOL, GpuRun, assert_scores_match, say
@@ -86,3 +87,31 @@ def test_f32_tile_size_does_not_change_scores():
     assert np.all(np.isfinite(ref))
     for (lo, hi), g in got.items():
         assert np.array_equal(g[lo:hi], ref[lo:hi]), f"rows {lo}..{hi}"
+
+
+def test_encode_workspace_without_room_for_small_items():
+    """head_dim 64: a workspace that holds the work list of 128-row items but not
+    that of the 64-row ones a small encode call prefers (as one sized before
+    there were 64-row items) gives the same cache; one that holds neither is
+    refused, and nothing is written."""
+    import torch
+    lens = [700, 33, 3000, 130]
+    inp = make_inputs(lens, [1] * len(lens), 512, 8, 2, 512, dtype="bf16", seed=740, variant="perturbed")
+    run = GpuRun(inp)
+    run.encode()
+    ref = run.cache_np().copy()
+    need = upr.upr_encode_workspace_bytes(run.model.handle, upr.segments(run.hoff, run.hoff_d))
+    items64, items128 = (8 * sum(-(-n // t) for n in lens) for t in (64, 128))
+    assert items64 < 2 * 512 and items128 < 512         # the 64-row list is the preferred one
+    least = need - 16 * items64 // 256 * 256 + -(-16 * items128 // 256) * 256
+    assert 16 * items64 % 256 == 0
+    for nbytes in (need - 1, least):
+        run.cache.zero_()
+        run.model.encode(run.X, run.hoff, run.hoff_d, run.cache,
+                         ws=torch.empty(nbytes, dtype=torch.uint8, device="cuda"))
+        assert np.array_equal(run.cache_np(), ref), f"{nbytes} of {need} bytes"
+    run.cache.zero_()
+    with pytest.raises(upr.UprError):
+        run.model.encode(run.X, run.hoff, run.hoff_d, run.cache,
+                         ws=torch.empty(least - 1, dtype=torch.uint8, device="cuda"))
+    assert not run.cache_np().any()

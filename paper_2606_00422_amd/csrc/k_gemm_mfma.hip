@@ -533,15 +533,19 @@ hipError_t launch_gemm_mx(const uint8_t* A, const uint8_t* A_scales, const uint8
 
 // Whether a residual update runs on small tiles with its LayerNorm (or score
 // head) as a launch of its own, instead of on whole-row tiles with it in the
-// epilogue.  Whole-row tiles are few and walk K with nobody beside them.  FFN
-// down (K > N): until 128-row tiles fill the device (2000 rows x 512, K 2048:
-// 29 us against 11.2 + 3.3; 16000 rows: 91 against 43 + 9.6).  O projection:
-// while the 64 x 64 tiles all run at once (2000 rows, K 512: 11.7 against
-// 5.6 + 3.3; 8000 rows: 15 against 11.7 + 5.9).
+// epilogue.  Whole-row tiles of 32 rows walk K with nobody beside them but take
+// the same time however many run at once: separate launches win where K is long
+// for the rows, and past one round of those tiles (K > 64), until 128-row tiles
+// fill the device.  us per layer of a ranking call (the other update unchanged), folded /
+// separate:
+//   FFN down (K > N): d 64, K 128: 2000 rows 24.9 / 24.8, 4000 25.4 / 26.6; d 192, K 384: 5000 39.2 / 38.5,
+//     8000 45.8 / 46.9; d 512, K 2048: 2000 82.9 / 61.0, 8000 127 / 114, 20000 330 / 256
+//   O projection: d 64: 500 rows 23.7 / 24.1, 8000 30.1 / 32.9, 16000 42.8 / 44.9; d 192: 2000 30.9 / 30.6,
+//     5000 38.5 / 40.6, 10000 58.2 / 57.1; d 512: 2000 61.0 / 58.2, 5000 89.6 / 90.3, 20000 256 / 249
 bool separate_layernorm(int64_t M, int N, int K) {
     const int64_t cus = gemm_detail::device_cus();
-    if (K > N) return (M + 127) / 128 < cus;
-    return ((M + 63) / 64) * (int64_t)((N + 63) / 64) <= 2 * cus;
+    if (M > 32 * cus) return K > 64 && (M + 127) / 128 < cus;
+    return M <= (K > N ? 4 * cus + cus * K / 25 : cus * K / 28);
 }
 
 // bf16 models: fp16 projection operands on the matrix cores.  Which tile is

@@ -22,8 +22,9 @@
 // of fp32 models.
 //
 // Measured (us per launch, back to back; large tiles -> this kernel): fp16
-// 2000 x 512, K 2048: 20.3 -> 11.2; K 512: 8.7 -> 5.6; 1000 x 2048, K 512:
-// 9.3 -> 6.3.  fp32 (FMA kernel -> this one) 2132 x 768, K 256: 37 -> 12.4;
+// 2000 x 512, K 2048: 20.3 -> 11.2; K 512: 8.7 -> 5.6 (in a call, on weights that
+// are not in L2 yet, the two average 12.0); 1000 x 2048, K 512: 9.3 -> 6.3.
+// fp32 (FMA kernel -> this one) 2132 x 768, K 256: 37 -> 12.4;
 // 128 x 256, K 256: 34 -> 4.2; 8000 x 2048, K 512: 315 -> 138 (121 TFLOP/s).
 //
 // fp32: a 128-byte row is 32 values; lane group g = lane / 16 takes 16-byte

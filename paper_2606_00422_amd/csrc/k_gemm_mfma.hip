@@ -4,9 +4,9 @@
 //
 // Block tile 256 (rows of A) x 256 (rows of W), K in steps of 64, eight
 // waves in a 2 (M) x 4 (N) grid, each owning 128 x 64 outputs = 4 x 2 MFMA
-// tiles (and 192, 128 or 64 rows for calls that fill the device better so).  The MFMA computes the transposed tile, C^T = W A^T (W as the
-// first operand), so each lane holds runs of four consecutive output
-// columns of one row.
+// tiles (and 192, 128 or 64 rows for calls that fill the device better so).
+// The MFMA computes the transposed tile, C^T = W A^T (W as the first operand),
+// so each lane holds runs of four consecutive output columns of one row.
 //
 // Main loop.  A and W tiles go straight from global memory into LDS
 // (buffer loads with the LDS bit: no staging registers; rows past the end
@@ -553,7 +553,8 @@ bool separate_layernorm(int64_t M, int N, int K) {
 // same bits).
 //  * 64 x 64 tiles (k_gemm_small.hip) while they all run at once, two to a
 //    compute unit: 4000 rows x 512, K 512, 504 tiles: 7.3 us against 10 on
-//    the best of the others; 3000 x 768, K 3072, 564 tiles: 38 against 31.5.
+//    the best of the others; 3000 x 768, K 3072, 564 tiles: 38 against 31.5
+//    (back to back).
 //  * Otherwise 256-column tiles of 64 to 256 rows, one to a compute unit,
 //    that run in rounds of as many tiles as there are compute units.  A round
 //    of 256-row tiles takes 1, of lower ones about 0.80, 0.60 and 0.42 (K

@@ -25,9 +25,9 @@
 //    per chunk.
 //  * The FFN down accumulators start at zero (the sum r + (acc + b) of the
 //    separate GEMM), so the residual after the O projection waits in HBM (the
-//    register file holds one such tile).  Tiles of whole 128 rows keep it,
-//    between launches too, in the order of the accumulators: every access is
-//    1 KB contiguous.
+//    register file holds one such tile).  Whole tiles, of 128 or 64 rows, keep
+//    it, between launches too, in the order of the accumulators: every access
+//    is 1 KB contiguous.
 //  * The last step stages 32 updated rows at a time in LDS and treats them as
 //    the row kernels do (row.h): one wave per row.
 //
@@ -36,9 +36,12 @@
 // 2 us of MFMAs at the clock they run at; removing GELU, or weights that hit
 // the first-level cache, would save 0.25 us each) and 60 the O projection and
 // the two ends, which move 1.1 MB a tile: 5 TB/s over the chip, the rate of a
-// large copy.  Tried and slower or no faster: the two waves of a SIMD half a
+// large copy.  128-row tiles at d 512 spill 29 to 42 registers (120 to 172 bytes
+// a lane), all but one to three of the reloads outside the chunk loop; 64-row
+// tiles none.  Tried and slower or no faster: the two waves of a SIMD half a
 // chunk apart with three chunk buffers (3.6 us a chunk, d 256 15% slower), the
-// O projection's residual read a pass ahead (registers spill).
+// O projection's residual read a pass ahead (more spills).  At d 256 four of
+// the eight waves have no output columns in the O projection and the FFN down.
 #include "gemm_tile.h"
 #include "row.h"
 

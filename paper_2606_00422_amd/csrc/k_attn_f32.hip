@@ -24,8 +24,8 @@
 //
 // Bound by the fp32 matrix rate (157 TFLOP/s nominal): per 16 keys a wave
 // issues D/2 MFMAs of 32 cycles and about 60 VALU instructions.  Ranking 4
-// users (150-450 rows, 300-700 candidates, 4 heads of 64): 20.6 us per layer,
-// 175 on the one-wave-per-row kernel.
+// users (150-450 rows, 300-700 candidates, 4 heads of 64): 21.2 us per layer
+// (20.7 with one chain per sum), 175 on the one-wave-per-row kernel.
 #include <type_traits>
 
 #include "attn_row.h"

@@ -26,6 +26,10 @@ CASES = [
     (768, 12, 1, 832, "bf16", 9000),        # rows past the whole-row tile
     (64, 2, 2, 192, "f32", 9000),
     (320, 5, 1, 448, "f32", 9000),
+    # narrow rows: LayerNorms folded into the residual updates or not by rows
+    # and K (FFN down apart to 3,584 and 4,956 rows and past 8,192)
+    (64, 1, 1, 256, "bf16", 20000),
+    (192, 3, 1, 384, "bf16", 20000),
 ]
 
 
